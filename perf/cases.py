@@ -283,6 +283,12 @@ def work(case):
         U = c["U"]
     elif c["routing"] == "tree":
         U = len(np.unique(_routes(c, 1, 0)))
+    elif c["router"] == "grouped":  # biased scores within the best half of the groups: counted on a draw
+        rng = np.random.default_rng(1)
+        s = 1 / (1 + np.exp(-rng.standard_normal((T, c["E"])))) + rng.uniform(-0.1, 0.1, c["E"])
+        grp = np.sort(s.reshape(T, 8, -1), -1)[:, :, -2:].sum(-1)
+        s[np.repeat(grp < np.sort(grp, -1)[:, 4:5], c["E"] // 8, 1)] = -1
+        U = len(np.unique(np.argsort(-s, 1)[:, :c["k"]]))
     else:
         U = round(c["E"] * (1 - (1 - c["k"] / c["E"]) ** T))
     n_bias = U * (2 * c["d_ff"] + c["d"]) * 4 if c["oai"] else 0
