@@ -61,6 +61,7 @@
 // K 16g..16g+15 and 64+16g..64+16g+15, so activation rows are stored in that
 // order (each 128-element chunk as four 32-byte lane runs).
 #include "device.hpp"
+#include "expert_common.hpp"
 #include "launch.hpp"
 #include "split.hpp"
 
@@ -85,9 +86,6 @@
 
 namespace ecospec {
 
-enum { FMT_BF16 = 0, FMT_FP8 = 1, FMT_MXFP4 = 2 };
-
-constexpr int kMacroK = 128;            // reduction elements per macro step
 constexpr int kMB = 4;                  // 16-token blocks per item
 constexpr int kTokGroup = 16 * kMB;     // tokens per item
 // An item's rows are cut into kWG slots: 16 rows (gate/up, with the same
@@ -104,7 +102,6 @@ constexpr int kEThreads = kPW * kWave;               // expert kernels
 constexpr int kBRowsPerPass = kEThreads / 16;        // activation rows staged per pass (16 threads per row)
 constexpr int kBPass = kTokGroup / kBRowsPerPass;    // passes per step
 static_assert(kWG % kPW == 0, "whole slots per wavefront");
-constexpr int kAuxNT = 2;               // nontemporal: streamed weights should not displace activations
 // Floats of one partial-sum slot: a workgroup's accumulators of the live token
 // blocks (a token group holds at most min(T, 64) tokens).
 constexpr int partial_floats(int T)
@@ -122,15 +119,6 @@ __device__ __forceinline__ long long ld_s64(const long long *p)
 {
     return *reinterpret_cast<const __attribute__((address_space(4))) long long *>(reinterpret_cast<uintptr_t>(p));
 }
-
-// kVecs: 16-byte vectors per lane in one 16 x 128 block of a tile; kBlocks:
-// 128-wide K blocks per macro step.  MXFP4 takes two blocks a step, so that a
-// step streams 2 KiB per tile like FP8 and pays its fixed per-step work (the
-// activation staging, the barrier, the item bookkeeping) over as many bytes.
-template <int FMT> struct Fmt;
-template <> struct Fmt<FMT_BF16>  { static constexpr int kVecs = 4, kBlocks = 1; };
-template <> struct Fmt<FMT_FP8>   { static constexpr int kVecs = 2, kBlocks = 1; };
-template <> struct Fmt<FMT_MXFP4> { static constexpr int kVecs = 1, kBlocks = 2; };
 
 // LDS geometry of one step's activation tile: 64 tokens x 128 * SB bf16
 // elements, block-major.  Block b of token row r is 256 bytes at
@@ -153,15 +141,6 @@ template <int FMT> struct WFrag {
     uint32_t code;                                 // MXFP4: the lane's e8m0 codes of a quad of blocks
     int shift;                                     // MXFP4: bit offset of the step's first block in `code`
 };
-
-// The scale operand of the scaled conversions (v_cvt_scalef32_*): the
-// instruction takes the operand's exponent field as an e8m0 code, so field 0
-// scales by 2^-127 and field 255 gives NaN, as the OCP MX definition of the
-// code does (checked on the device against the exact scale value for all 256
-// codes and all 256 FP4 code pairs: identical results).  The code shifted into
-// the exponent field is therefore the operand for every code, with no special
-// cases.
-__device__ __forceinline__ float e8m0_scale_operand(uint32_t code) { return __uint_as_float((code & 0xffu) << 23); }
 
 // MX FP8 activation quantisation.  A block's scale exponent from its largest
 // magnitude: E = floor(log2(amax)) - 8 (448, the largest e4m3fn value, is
@@ -197,34 +176,12 @@ __device__ __forceinline__ uint32_t e4m3_code(float v)
     return sign | code;
 }
 
-// bf16 A operand of sub-step s (the lane's weights 8s .. 8s+7 of a block;
-// MXFP4: sub-step s of block s / 4).
-// Exact: FP8 codes as they are (the converter's scale operand only takes a
-// power of two, so the 128x128 block scale multiplies the fp32 partial sum of
-// the step instead); MXFP4 codes times their 2^e8m0 group scale.
+// bf16 A operand of sub-step s of a macro step (MXFP4: sub-step s % 4 of block s / 4).
 template <int FMT>
 __device__ __forceinline__ bf16x8 decode_a(const WFrag<FMT> &f, int s)
 {
-    if constexpr (FMT == FMT_BF16) {
-        return __builtin_bit_cast(bf16x8, f.v[s]);
-    } else if constexpr (FMT == FMT_FP8) {
-        const uint32_t w0 = f.v[s >> 1][(s & 1) * 2], w1 = f.v[s >> 1][(s & 1) * 2 + 1];
-        u32x4 o;
-        o[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w0, 1.0f, false));
-        o[1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w0, 1.0f, true));
-        o[2] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w1, 1.0f, false));
-        o[3] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w1, 1.0f, true));
-        return __builtin_bit_cast(bf16x8, o);
-    } else {
-        const uint32_t w = f.v[s >> 2][s & 3];
-        const float sc = e8m0_scale_operand(f.code >> (f.shift + 8 * (s >> 2)));
-        u32x4 o;
-        o[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(w, sc, 0));
-        o[1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(w, sc, 1));
-        o[2] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(w, sc, 2));
-        o[3] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(w, sc, 3));
-        return __builtin_bit_cast(bf16x8, o);
-    }
+    const float sc = FMT == FMT_MXFP4 ? e8m0_scale_operand(f.code >> (f.shift + 8 * (s >> 2))) : 1.f;
+    return decode8<FMT>(f.v + (FMT == FMT_MXFP4 ? s >> 2 : 0), s & 3, sc);
 }
 
 // ----------------------------------------------------------------------------- launch geometry
@@ -693,27 +650,6 @@ __device__ __forceinline__ ItemBias load_bias(const FfnParams &P, const ItemDesc
     if (a.b_gate) b.g = *reinterpret_cast<const f32x4 *>(a.b_gate + (size_t)d.e * a.d_ff + row);
     if (a.b_up) b.u = *reinterpret_cast<const f32x4 *>(a.b_up + (size_t)d.e * a.d_ff + row);
     return b;
-}
-
-// g * sigmoid(s * g) with the hardware exp2 and reciprocal (about 2 ulp in
-// fp32, far below the bf16 rounding of H): g / (1 + e^(-s g)).  Large -s g
-// gives 1 + inf, whose reciprocal is 0, and NaN stays NaN, as in the
-// division form.
-__device__ __forceinline__ float gated(float g, float s)
-{
-    return g * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-s * g * 1.44269504088896341f));
-}
-
-// h from the gate and up values of one row (biases already added):
-// act 0 silu(g) * u; act 1 (GPT-OSS) with g capped at limit and u clamped to
-// [-limit, limit], g * sigmoid(alpha * g) * (u + 1).  The comparisons keep NaN.
-__device__ __forceinline__ float activate(const VerifyArgs &a, float g, float u)
-{
-    if (a.act == 0) return gated(g, 1.f) * u;
-    if (g > a.limit) g = a.limit;
-    if (u > a.limit) u = a.limit;
-    if (u < -a.limit) u = -a.limit;
-    return gated(g, a.alpha) * (u + 1.f);
 }
 
 // Finishes the accumulators of an item held by wavefront pw, which owns slots
@@ -1785,6 +1721,7 @@ static hipError_t launch_fmt(const VerifyArgs &args, uint8_t *ws_base, const Ver
 hipError_t launch_verify(const VerifyArgs &a, void *workspace, const VerifyWorkspace &ws, hipStream_t stream,
                          hipEvent_t const *events)
 {
+    if (small_verify(a, ws.workers)) return launch_small_verify(a, workspace, ws, stream, events);
     uint8_t *base = static_cast<uint8_t *>(workspace);
     switch (a.fmt) {
     case FMT_BF16: return launch_fmt<FMT_BF16, false>(a, base, ws, stream, events);

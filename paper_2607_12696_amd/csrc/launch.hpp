@@ -88,6 +88,12 @@ VerifyWorkspace verify_workspace(int d, int d_ff, int T, int k, bool shared, boo
 hipError_t launch_verify(const VerifyArgs &a, void *workspace, const VerifyWorkspace &ws, hipStream_t stream,
                          hipEvent_t const *events = nullptr);
 
+// Small calls (expert_small.hip): whether a call takes that path, and its launches (same marks).
+constexpr int kSmallT = 16;  // most tokens of a small call
+bool small_verify(const VerifyArgs &a, int workers);
+hipError_t launch_small_verify(const VerifyArgs &a, void *workspace, const VerifyWorkspace &ws, hipStream_t stream,
+                               hipEvent_t const *events);
+
 // Packed (streaming) weight layout; see pack.hip.
 size_t packed_matrix_bytes(int fmt, int N, int K);
 size_t packed_scale_bytes(int fmt, int N, int K);
