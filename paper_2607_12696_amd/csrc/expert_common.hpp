@@ -71,13 +71,18 @@ __device__ __forceinline__ float gated(float g, float s)
 // h from the gate and up values of one row (biases already added):
 // act 0 silu(g) * u; act 1 (GPT-OSS) with g capped at limit and u clamped to
 // [-limit, limit], g * sigmoid(alpha * g) * (u + 1).  The comparisons keep NaN.
+__device__ __forceinline__ float activate(int act, float alpha, float limit, float g, float u)
+{
+    if (act == 0) return gated(g, 1.f) * u;
+    if (g > limit) g = limit;
+    if (u > limit) u = limit;
+    if (u < -limit) u = -limit;
+    return gated(g, alpha) * (u + 1.f);
+}
+
 __device__ __forceinline__ float activate(const VerifyArgs &a, float g, float u)
 {
-    if (a.act == 0) return gated(g, 1.f) * u;
-    if (g > a.limit) g = a.limit;
-    if (u > a.limit) u = a.limit;
-    if (u < -a.limit) u = -a.limit;
-    return gated(g, a.alpha) * (u + 1.f);
+    return activate(a.act, a.alpha, a.limit, g, u);
 }
 
 }  // namespace ecospec

@@ -50,16 +50,43 @@ constexpr int kSThreads = kSWaves * kWave;
 constexpr int kSmallSlots = kSmallT * 64;  // routed slots: k <= 64
 constexpr int kPieceFloats = 2 * kWave * 4;  // partial sums of one piece of a cut item (gate and up tile)
 
+// A divisor known before the launch: x / d for x < 2^31 as a multiplication (the 31-bit case of the
+// round-up method: m = ceil(2^(31 + s) / d) with s = ceil(log2 d) fits 32 bits and is exact).
+struct Divisor {
+    uint32_t d, m, s;
+    __device__ __forceinline__ uint32_t operator()(uint32_t x) const { return (uint32_t)(((uint64_t)x * m) >> (31 + s)); }
+};
+
+static Divisor divisor(uint32_t d)
+{
+    uint32_t s = 0;
+    while ((1ull << s) < d) ++s;
+    return Divisor{d, (uint32_t)((((uint64_t)1 << (31 + s)) + d - 1) / d), s};
+}
+
+// Where one kind of expert's weights lie (routed, or the shared one): tile 0 and tile 1 of item 0.
+struct SmallWeights {
+    const uint8_t *w0, *w1, *s0, *s1;
+    uint32_t expert;            // bytes from one expert's matrix (pair) to the next
+    uint32_t range0, range1;    // bytes of an expert that are readable from w0 and w1 on
+    uint32_t kstride, tstride;  // bytes from one K block, and one item, to the next
+};
+
 struct SmallParams {
-    VerifyArgs a;
-    int N, K;              // rows and reduction length of one streamed matrix
-    int nblocks;           // 128-wide K blocks
-    int tiles;             // items per expert
-    uint32_t mat_bytes, sc_bytes;
-    int workers;
+    SmallWeights wts[2];   // the routed experts', the shared expert's
+    const int32_t *topk_idx;
+    const void *in;        // x or H
+    void *out;             // H or O
     float *pieces;         // [workers][2][kPieceFloats]
+    const float *b_gate, *b_up;
+    int T, k, S, E, U_extra;  // U_extra: 1 with a shared expert
+    int K, nblocks, ldo;      // reduction length, its 128-wide blocks, columns of a row of `out`
+    uint32_t sc_bytes, sstride;  // bytes of an expert's scales; MXFP4: of one item's
+    Divisor dG, dtiles, dk;   // workgroups, items per expert, top-k
     int gu_tiles, gu_rounds;  // the gate/up launch's items per expert and rounds per item
     uint32_t gu_bytes;        // and bytes per item
+    int act;
+    float alpha, limit;
 };
 
 // Weights of one round of a wavefront: one 16 x 128 block of each of its two tiles.
@@ -92,27 +119,31 @@ void expert_small_kernel(SmallParams P)
     __shared__ int sidx[kSmallSlots];             // expert of each routed slot
     __shared__ int slots[kSWaves][kSmallT];       // slots of the current expert (one copy per wavefront)
     __shared__ f32x4 red[2][kSWaves][2][kWave];   // an item's partial sums, double-buffered
-    const VerifyArgs &a = P.a;
-    const uint32_t G = (uint32_t)P.workers;
+    const uint32_t G = P.dG.d;
     // Ranges XCD-major: the workgroups sharing an L2 work on neighbouring items.
     const uint32_t w = G % 8 == 0 ? (blockIdx.x % 8) * (G / 8) + blockIdx.x / 8 : blockIdx.x;
     const int tid = threadIdx.x, lane = lane_id(), col = lane & 15, grp = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-    const int S = a.T * a.k;
+    const int S = P.S;
 
     // Distinct experts.
     if (tid < 32) emask[tid] = 0u;
-    int e0 = tid < S ? a.topk_idx[tid] : -1, e1 = tid + kSThreads < S ? a.topk_idx[tid + kSThreads] : -1;
+    const int e0 = tid < S ? P.topk_idx[tid] : -1, e1 = tid + kSThreads < S ? P.topk_idx[tid + kSThreads] : -1;
+    // Bring every line of the arguments into the scalar cache now, in the shadow of the slots' load: read
+    // where they are used, each line would cost its own round trip before the first weight load.
+    asm volatile("" ::"s"(P.wts[0].w0), "s"(P.wts[1].w0), "s"(P.wts[1].tstride), "s"(P.in), "s"(P.K), "s"(P.dk.s), "s"(P.limit));
     __syncthreads();
     if (tid < S) sidx[tid] = e0;
-    if (tid + kSThreads < S) sidx[tid + kSThreads] = e1;
-    if ((unsigned)e0 < (unsigned)a.E) atomicOr(&emask[e0 >> 5], 1u << (e0 & 31));
-    if ((unsigned)e1 < (unsigned)a.E) atomicOr(&emask[e1 >> 5], 1u << (e1 & 31));
+    if ((unsigned)e0 < (unsigned)P.E) atomicOr(&emask[e0 >> 5], 1u << (e0 & 31));
+    if (S > kSThreads) {
+        if (tid + kSThreads < S) sidx[tid + kSThreads] = e1;
+        if ((unsigned)e1 < (unsigned)P.E) atomicOr(&emask[e1 >> 5], 1u << (e1 & 31));
+    }
     __syncthreads();
     const uint32_t mword = lane < 32 ? emask[lane] : 0u;
     const int mcount = __popc(mword), mincl = wave_inclusive_sum(mcount);
     const int U = __builtin_amdgcn_readlane(mincl, 63);
-    const uint32_t n_exp = (uint32_t)(U + (a.sh_gate ? 1 : 0));
+    const uint32_t n_exp = (uint32_t)(U + P.U_extra);
     // Id of the u-th distinct expert (wave-uniform; -1: the shared expert).
     auto expert_of = [&](int u) -> int {
         if (u >= U) return -1;
@@ -124,67 +155,77 @@ void expert_small_kernel(SmallParams P)
         return 32 * wl + (int)__builtin_ctzll(hit);
     };
 
-    const split::SmallSplit gs = split::small_split(n_exp * (uint32_t)P.gu_tiles, (uint32_t)P.gu_rounds, P.gu_bytes, G);
-    const split::SmallSplit sp = DOWN ? split::SmallSplit{n_exp * (uint32_t)P.tiles, 1u} : gs;
-    const uint32_t x0 = sp.first(w, G), x1 = sp.first(w + 1, G);
+    const split::SmallSplit gs = split::small_split(n_exp * (uint32_t)P.gu_tiles, (uint32_t)P.gu_rounds, P.gu_bytes, G, P.dG);
+    const split::SmallSplit sp = DOWN ? split::SmallSplit{n_exp * P.dtiles.d, 1u} : gs;
+    const uint32_t x0 = P.dG(sp.units * w), x1 = P.dG(sp.units * (w + 1));
     if (x0 >= x1) return;
-    const uint32_t t0 = x0 / sp.per_item, tl = (x1 - 1) / sp.per_item;
-    const int n = (int)(tl - t0) + 1;                                     // items of the range
-    const int jfirst = sp.per_item == 1 ? 0 : (int)(x0 - t0 * sp.per_item);  // first round of the first item
-    const int jlast = sp.per_item == 1 ? J : (int)(x1 - tl * sp.per_item);   // end round of the last item
+    uint32_t t0 = x0, tl = x1 - 1;
+    int jfirst = 0, jlast = J;  // first round of the first item, end round of the last item
+    if (sp.per_item != 1) {
+        t0 = x0 / sp.per_item;
+        tl = (x1 - 1) / sp.per_item;
+        jfirst = (int)(x0 - t0 * sp.per_item);
+        jlast = (int)(x1 - tl * sp.per_item);
+    }
+    const int n = (int)(tl - t0) + 1;  // items of the range
+    const int nkb = P.nblocks, tiles = (int)P.dtiles.d;
+    const int kb0 = nkb * wave / kSWaves, kcount = nkb * (wave + 1) / kSWaves - kb0;  // this wavefront's K blocks
+    const int u0 = (int)P.dtiles(t0), it0 = (int)t0 - u0 * tiles;
 
-    // Load cursor: the item whose weights are being issued.
-    const int nkb = P.nblocks;
-    const int kb0 = nkb * wave / kSWaves, kbe = nkb * (wave + 1) / kSWaves;  // this wavefront's K blocks
-    const bool sh_pair = DOWN ? a.down_pair : a.sh_gu_pair, ro_pair = DOWN ? a.down_pair : a.gu_pair;
-    int cu = (int)(t0 / (uint32_t)P.tiles), ct = (int)(t0 % (uint32_t)P.tiles), ci = 0;  // expert, tile, item of the range
+    // Load cursor: the item whose weights are being issued.  Offsets are scalar: a load's address is its
+    // descriptor's base + wj + the lane's 16 bytes.  A dead load (past the range, or a block another
+    // wavefront has) moves every lane out of the descriptor's range and reads zeros; its scalar offset is 0,
+    // since the range check compares with the range less that offset.
     rsrc_t ra0, ra1, rs0, rs1;
-    uint32_t tstride, toff, kstride;
+    uint32_t kstride, tstride;
     auto set_expert = [&](int u) {
         const int e = expert_of(u);
-        const bool sh = e < 0, pair = sh ? sh_pair : ro_pair;
-        const size_t ee = sh ? 0 : (size_t)e;
-        const uint8_t *wa = DOWN ? (sh ? a.sh_down : a.w_down) : (sh ? a.sh_gate : a.w_gate);
-        const size_t mat = (size_t)P.mat_bytes * (!DOWN && pair ? 2 : 1);
-        ra0 = ra1 = make_rsrc(wa + ee * mat, (uint32_t)mat);
-        if (!DOWN && !pair) ra1 = make_rsrc((sh ? a.sh_up : a.w_up) + ee * mat, (uint32_t)mat);
-        kstride = pair ? 2 * BLK : BLK;
-        tstride = (uint32_t)nkb * BLK * (DOWN || pair ? 2u : 1u);
-        toff = pair ? BLK : DOWN ? (uint32_t)nkb * BLK : 0u;
+        const SmallWeights &q = P.wts[e < 0 ? 1 : 0];
+        const size_t ee = e < 0 ? 0 : (size_t)e;
+        ra0 = make_rsrc(q.w0 + ee * q.expert, q.range0);
+        ra1 = make_rsrc(q.w1 + ee * q.expert, q.range1);
+        kstride = q.kstride;
+        tstride = q.tstride;
         if constexpr (FMT != FMT_BF16) {
-            const uint8_t *s0 = static_cast<const uint8_t *>(DOWN ? (sh ? a.sh_s_down : a.s_down) : (sh ? a.sh_s_gate : a.s_gate));
-            const uint8_t *s1 = static_cast<const uint8_t *>(DOWN ? (sh ? a.sh_s_down : a.s_down) : (sh ? a.sh_s_up : a.s_up));
-            rs0 = make_rsrc(s0 + ee * P.sc_bytes, P.sc_bytes);
-            rs1 = make_rsrc(s1 + ee * P.sc_bytes, P.sc_bytes);
+            rs0 = make_rsrc(q.s0 + ee * P.sc_bytes, P.sc_bytes);
+            rs1 = make_rsrc(q.s1 + ee * P.sc_bytes, P.sc_bytes);
         }
     };
+    set_expert(u0);
+    int ci = 0, ct = it0, cu = u0, jlo = jfirst, jhi = min(n == 1 ? jlast : J, kcount);
+    uint32_t wj = (uint32_t)ct * tstride + (uint32_t)kb0 * kstride;
     auto advance = [&]() {
         ++ci;
-        if (++ct == P.tiles) {
+        if (++ct == tiles) {
             ct = 0;
             if (ci < n) set_expert(++cu);
         }
+        jlo = 0;
+        jhi = ci < n ? min(ci == n - 1 ? jlast : J, kcount) : 0;
+        wj = (uint32_t)ct * tstride + (uint32_t)kb0 * kstride;
     };
 
     SmallSlot<FMT> ring[D];
+    const uint32_t lane16 = (uint32_t)lane * 16u, lane4 = (uint32_t)lane * 4u;
     auto issue = [&](int slot, int j) {
-        const int kb = kb0 + j;
-        const bool ok = j < J && ci < n && kb < kbe && (ci > 0 || j >= jfirst) && (ci < n - 1 || j < jlast);
-        const uint32_t off = (uint32_t)ct * tstride + (uint32_t)kb * kstride + (uint32_t)lane * 16u;
-        const uint32_t o0 = ok ? off : kOff, o1 = ok ? off + toff : kOff;
+        const bool live = j >= jlo && j < jhi;
+        const uint32_t dead = live ? 0u : kOff, vo = lane16 | dead;
+        const int wo = live ? (int)wj : 0;
 #pragma unroll
-        for (int i = 0; i < NV; ++i) ring[slot].v[0][i] = load16<kAuxNT>(ra0, o0 + 1024u * i);
+        for (int i = 0; i < NV; ++i)
+            ring[slot].v[0][i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(ra0, (int)(vo + 1024u * i), wo, kAuxNT));
 #pragma unroll
-        for (int i = 0; i < NV; ++i) ring[slot].v[1][i] = load16<kAuxNT>(ra1, o1 + 1024u * i);
+        for (int i = 0; i < NV; ++i)
+            ring[slot].v[1][i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(ra1, (int)(vo + 1024u * i), wo, kAuxNT));
+        wj += kstride;
         if constexpr (FMT == FMT_FP8) {  // 128 x 128 block scales: an item's rows lie in one row block
-            const uint32_t so = ok ? ((uint32_t)(ct / (DOWN ? 4 : 8)) * (uint32_t)nkb + (uint32_t)kb) * 4u : kOff;
-            ring[slot].sc[0] = __builtin_amdgcn_raw_buffer_load_b32(rs0, (int)so, 0, 0);
-            ring[slot].sc[1] = DOWN ? ring[slot].sc[0] : __builtin_amdgcn_raw_buffer_load_b32(rs1, (int)so, 0, 0);
+            const int so = live ? ((ct / (DOWN ? 4 : 8)) * nkb + kb0 + j) * 4 : 0;
+            ring[slot].sc[0] = __builtin_amdgcn_raw_buffer_load_b32(rs0, (int)dead, so, 0);
+            ring[slot].sc[1] = DOWN ? ring[slot].sc[0] : __builtin_amdgcn_raw_buffer_load_b32(rs1, (int)dead, so, 0);
         } else if constexpr (FMT == FMT_MXFP4) {
-            const uint32_t nq = (uint32_t)((nkb + 3) / 4);
-            const uint32_t so = (uint32_t)ct * (DOWN ? 2u : 1u) * nq * 256u + (uint32_t)(kb >> 2) * 256u + (uint32_t)lane * 4u;
-            ring[slot].sc[0] = __builtin_amdgcn_raw_buffer_load_b32(rs0, (int)(ok ? so : kOff), 0, 0);
-            ring[slot].sc[1] = __builtin_amdgcn_raw_buffer_load_b32(rs1, (int)(ok ? so + (DOWN ? nq * 256u : 0u) : kOff), 0, 0);
+            const int so = live ? ct * (int)P.sstride + ((kb0 + j) >> 2) * 256 : 0;
+            ring[slot].sc[0] = __builtin_amdgcn_raw_buffer_load_b32(rs0, (int)(lane4 | dead), so, 0);
+            ring[slot].sc[1] = __builtin_amdgcn_raw_buffer_load_b32(rs1, (int)(lane4 | dead), so, 0);
         }
     };
 
@@ -192,13 +233,12 @@ void expert_small_kernel(SmallParams P)
     // token col's elements kb * 128 + 32 grp .. + 31 of each block.
     int myslot = -1, ce = -1;
     bf16x8 bx[J][4];
-    const uint32_t brow = (uint32_t)(DOWN ? a.d_ff : a.d) * 2u;
-    const rsrc_t rb = make_rsrc(DOWN ? static_cast<const void *>(a.h) : static_cast<const void *>(a.x),
-                                (uint32_t)(DOWN ? S + (a.sh_gate ? a.T : 0) : a.T) * brow);
+    const uint32_t brow = (uint32_t)P.K * 2u;
+    const rsrc_t rb = make_rsrc(P.in, (uint32_t)(DOWN ? S + P.U_extra * P.T : P.T) * brow);
     auto load_b = [&](int u) {
         ce = expert_of(u);
         if (ce < 0) {
-            myslot = col < a.T ? S + col : -1;
+            myslot = col < P.T ? S + col : -1;
         } else {
             int cnt = 0;
             for (int base = 0; base < S; base += kWave) {
@@ -211,34 +251,37 @@ void expert_small_kernel(SmallParams P)
             __builtin_amdgcn_wave_barrier();  // the same wavefront's LDS accesses stay in order
             myslot = col < cnt ? slots[wave][col] : -1;
         }
-        const uint32_t row = (uint32_t)(DOWN ? myslot : ce < 0 ? myslot - S : (int)((uint32_t)myslot / (uint32_t)a.k));
+        const uint32_t row = (uint32_t)(DOWN ? myslot : ce < 0 ? myslot - S : (int)P.dk((uint32_t)myslot & 0x7fffffffu));
+        const uint32_t off = myslot >= 0 ? row * brow + 64u * grp : kOff;
 #pragma unroll
         for (int j = 0; j < J; ++j) {
-            const int k0 = (kb0 + j) * kMacroK + 32 * grp;  // K % 32 == 0: a chunk is all in or all out
-            const uint32_t off = myslot >= 0 && kb0 + j < kbe && k0 < P.K ? row * brow + (uint32_t)k0 * 2u : kOff;
+            const int k0 = (kb0 + j) * kMacroK;  // K % 32 == 0: a lane's chunk is all in or all out
+            const uint32_t vo = j < kcount && k0 + 32 * grp < P.K ? off : kOff;
+            const int so = j < kcount ? 2 * k0 : 0;
 #pragma unroll
-            for (int s = 0; s < 4; ++s) bx[j][s] = __builtin_bit_cast(bf16x8, load16<0>(rb, off + 16u * s));
+            for (int s = 0; s < 4; ++s)
+                bx[j][s] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rb, (int)(vo + 16u * s), so, 0));
         }
         if (DOWN && gs.per_item > 1) {
             // H columns of gate/up items that were cut between workgroups: add their pieces.  A rolled loop:
             // the code is cold and few items are cut (at most one per workgroup boundary).
 #pragma unroll 1
             for (int h = 0; h < 2 * J; ++h) {
-                const int kb = kb0 + h / 2, n0 = kb * kMacroK + 32 * grp + 16 * (h & 1);  // this lane's 16 columns
+                const int n0 = (kb0 + h / 2) * kMacroK + 32 * grp + 16 * (h & 1);  // this lane's 16 columns
                 const uint32_t ib = ((uint32_t)u * (uint32_t)P.gu_tiles + (uint32_t)(n0 / 16)) * gs.per_item;
-                const bool in = kb < kbe && n0 < P.K;
+                const bool in = h / 2 < kcount && n0 < P.K;
                 const uint32_t w0 = in ? gs.owner(ib, G) : 0u, w1 = in ? gs.owner(ib + gs.per_item - 1, G) : 0u;
                 if (w0 == w1) continue;
                 f32x4 g[4], up[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const size_t o = (size_t)ce * a.d_ff + n0 + 4 * q;
-                    g[q] = ce >= 0 && a.b_gate ? *reinterpret_cast<const f32x4 *>(a.b_gate + o) : f32x4{0.f, 0.f, 0.f, 0.f};
-                    up[q] = ce >= 0 && a.b_up ? *reinterpret_cast<const f32x4 *>(a.b_up + o) : f32x4{0.f, 0.f, 0.f, 0.f};
+                    const size_t o = (size_t)ce * P.K + n0 + 4 * q;
+                    g[q] = ce >= 0 && P.b_gate ? *reinterpret_cast<const f32x4 *>(P.b_gate + o) : f32x4{0.f, 0.f, 0.f, 0.f};
+                    up[q] = ce >= 0 && P.b_up ? *reinterpret_cast<const f32x4 *>(P.b_up + o) : f32x4{0.f, 0.f, 0.f, 0.f};
                 }
                 for (uint32_t v = w0; v <= w1; ++v) {
-                    const uint32_t f = gs.first(v, G);
-                    if (f >= gs.first(v + 1, G)) continue;  // a workgroup without units
+                    const uint32_t f = P.dG(gs.units * v);
+                    if (f >= P.dG(gs.units * (v + 1))) continue;  // a workgroup without units
                     const float *src = P.pieces + ((size_t)v * 2 + split::small_piece(f, ib)) * kPieceFloats + col * 4;
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
@@ -251,7 +294,7 @@ void expert_small_kernel(SmallParams P)
                 for (int q = 0; q < 4; ++q) {
                     float v[4];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) v[i] = activate(a, g[q][i], up[q][i]);
+                    for (int i = 0; i < 4; ++i) v[i] = activate(P.act, P.alpha, P.limit, g[q][i], up[q][i]);
                     pk[q >> 1][2 * (q & 1)] = pack_bf16x2(v[0], v[1]);
                     pk[q >> 1][2 * (q & 1) + 1] = pack_bf16x2(v[2], v[3]);
                 }
@@ -265,16 +308,15 @@ void expert_small_kernel(SmallParams P)
         }
     };
 
-    set_expert(cu);
-    int bu = cu, bt = ct;  // expert and tile being contracted
+    // Pipeline prologue: the first item's weights, the activations, then the rest of the ring.
+    int bu = u0, bt = it0;  // expert and tile being contracted
 #pragma unroll
     for (int q = 0; q < D - 1; ++q) {
         if (q > 0 && q % JU == 0) advance();
         issue(q, q % JU);
+        if (q == (J < D - 1 ? J : D - 1) - 1) load_b(bu);
     }
-    load_b(bu);
-
-    const bool biased = !DOWN && (a.b_gate != nullptr || a.b_up != nullptr);
+    const bool biased = !DOWN && (P.b_gate != nullptr || P.b_up != nullptr);
     for (int i0 = 0; i0 < n; i0 += PU) {
 #pragma unroll
         for (int p = 0; p < PU; ++p) {
@@ -282,9 +324,9 @@ void expert_small_kernel(SmallParams P)
             const bool mine = wave == (i & (kSWaves - 1));  // this wavefront finishes the item
             f32x4 gb = f32x4{0.f, 0.f, 0.f, 0.f}, ub = gb;
             if (biased && mine && i < n && ce >= 0) {
-                const size_t o = (size_t)ce * a.d_ff + 16 * bt + 4 * grp;
-                if (a.b_gate) gb = *reinterpret_cast<const f32x4 *>(a.b_gate + o);
-                if (a.b_up) ub = *reinterpret_cast<const f32x4 *>(a.b_up + o);
+                const size_t o = (size_t)ce * P.ldo + 16 * bt + 4 * grp;
+                if (P.b_gate) gb = *reinterpret_cast<const f32x4 *>(P.b_gate + o);
+                if (P.b_up) ub = *reinterpret_cast<const f32x4 *>(P.b_up + o);
             }
             f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
             const int jl = i == 0 ? jfirst : 0, jh = i == n - 1 ? jlast : J;
@@ -329,7 +371,7 @@ void expert_small_kernel(SmallParams P)
                     }
                     if (DOWN) {
                         if (myslot >= 0) {
-                            float *dst = a.o + (size_t)myslot * a.d + 32 * bt + 4 * grp;
+                            float *dst = static_cast<float *>(P.out) + (size_t)myslot * P.ldo + 32 * bt + 4 * grp;
                             *reinterpret_cast<f32x4 *>(dst) = r0;
                             *reinterpret_cast<f32x4 *>(dst + 16) = r1;
                         }
@@ -339,8 +381,8 @@ void expert_small_kernel(SmallParams P)
                             r1 += ub;
                             float h[4];
 #pragma unroll
-                            for (int r = 0; r < 4; ++r) h[r] = activate(a, r0[r], r1[r]);
-                            *reinterpret_cast<u32x2 *>(a.h + (size_t)myslot * a.d_ff + 16 * bt + 4 * grp) =
+                            for (int r = 0; r < 4; ++r) h[r] = activate(P.act, P.alpha, P.limit, r0[r], r1[r]);
+                            *reinterpret_cast<u32x2 *>(static_cast<uint16_t *>(P.out) + (size_t)myslot * P.ldo + 16 * bt + 4 * grp) =
                                 u32x2{pack_bf16x2(h[0], h[1]), pack_bf16x2(h[2], h[3])};
                         }
                     } else {
@@ -349,7 +391,7 @@ void expert_small_kernel(SmallParams P)
                         *reinterpret_cast<f32x4 *>(dst + kPieceFloats / 2) = r1;
                     }
                 }
-                if (++bt == P.tiles) {
+                if (++bt == tiles) {
                     bt = 0;
                     if (i + 1 < n) load_b(++bu);
                 }
@@ -463,9 +505,9 @@ __global__ __launch_bounds__(256) void combine_small_kernel(VerifyArgs a)
 // ----------------------------------------------------------------------------- host side
 
 template <int FMT, bool DOWN>
-static hipError_t launch_projection(const SmallParams &p, hipStream_t stream)
+static hipError_t launch_projection(const SmallParams &p, int workers, hipStream_t stream)
 {
-    const dim3 grid(p.workers), block(kSThreads);
+    const dim3 grid(workers), block(kSThreads);
     switch ((p.nblocks + kSWaves - 1) / kSWaves) {
 #define SMALL_CASE(J)                                                                          \
     case J:                                                                                    \
@@ -485,7 +527,28 @@ bool small_verify(const VerifyArgs &a, int workers)
     // The split's arithmetic is 32-bit.
     const uint64_t n_exp = (uint64_t)(a.E < a.T * a.k ? a.E : a.T * a.k) + 1;
     const uint64_t units = n_exp * ((uint64_t)(a.d_ff / 16) * ((nu + kSWaves - 1) / kSWaves) + a.d / 32);
-    return units * (uint64_t)workers < (1ull << 31);
+    return units * ((uint64_t)workers + 1) < (1ull << 31);
+}
+
+// The weights of the routed or of the shared expert for one launch: `w` (and, unpaired gate/up, `w2`).
+template <int FMT>
+static SmallWeights small_weights(bool down, bool pair, const uint8_t *w, const uint8_t *w2, const void *s, const void *s2, int N,
+                                  int K)
+{
+    constexpr uint32_t BLK = 1024u * Fmt<FMT>::kVecs;
+    const uint32_t mat = (uint32_t)packed_matrix_bytes(FMT, N, K), nkb = (uint32_t)(K + kMacroK - 1) / kMacroK;
+    SmallWeights q{};
+    if (!w) return q;
+    q.s0 = static_cast<const uint8_t *>(s);
+    q.s1 = static_cast<const uint8_t *>(s2);
+    q.w0 = w;
+    q.kstride = pair ? 2 * BLK : BLK;
+    q.tstride = nkb * BLK * (down || pair ? 2 : 1);
+    const uint32_t toff = pair ? BLK : down ? nkb * BLK : 0;  // tile 1's first block, from tile 0's
+    q.w1 = (!down && !pair ? w2 : w) + toff;
+    q.expert = q.range0 = mat * (!down && pair ? 2u : 1u);
+    q.range1 = q.range0 - toff;
+    return q;
 }
 
 template <int FMT>
@@ -493,36 +556,58 @@ static hipError_t launch_small_fmt(const VerifyArgs &args, uint8_t *ws_base, con
                                    hipEvent_t const *events)
 {
     auto mark = [&](int i) { return events && events[i] ? hipEventRecord(events[i], stream) : hipSuccess; };
+    VerifyArgs a = args;
+    a.h = reinterpret_cast<uint16_t *>(ws_base + ws.h_offset);
+    a.o = reinterpret_cast<float *>(ws_base + ws.o_offset);
     SmallParams p{};
-    p.a = args;
-    p.a.h = reinterpret_cast<uint16_t *>(ws_base + ws.h_offset);
-    p.a.o = reinterpret_cast<float *>(ws_base + ws.o_offset);
-    p.workers = ws.workers;
+    p.topk_idx = a.topk_idx;
     p.pieces = reinterpret_cast<float *>(ws_base + ws.p_offset);
-    const VerifyArgs &a = p.a;
-    p.N = a.d_ff;
-    p.K = a.d;
-    p.nblocks = (a.d + kMacroK - 1) / kMacroK;
-    p.tiles = a.d_ff / 16;
-    p.mat_bytes = (uint32_t)packed_matrix_bytes(FMT, a.d_ff, a.d);
-    p.sc_bytes = (uint32_t)packed_scale_bytes(FMT, a.d_ff, a.d);
-    p.gu_tiles = p.tiles;
+    p.b_gate = a.b_gate;
+    p.b_up = a.b_up;
+    p.T = a.T;
+    p.k = a.k;
+    p.S = a.T * a.k;
+    p.E = a.E;
+    p.U_extra = a.sh_gate ? 1 : 0;
+    p.dG = divisor((uint32_t)ws.workers);
+    p.dk = divisor((uint32_t)a.k);
+    p.act = a.act;
+    p.alpha = a.alpha;
+    p.limit = a.limit;
+
+    auto geometry = [&](bool down, int N, int K) {
+        p.K = K;
+        p.ldo = N;
+        p.nblocks = (K + kMacroK - 1) / kMacroK;
+        p.dtiles = divisor((uint32_t)(down ? N / 32 : N / 16));
+        p.sc_bytes = (uint32_t)packed_scale_bytes(FMT, N, K);
+        p.sstride = (down ? 2u : 1u) * (uint32_t)((p.nblocks + 3) / 4) * 256u;
+    };
+    geometry(false, a.d_ff, a.d);
+    p.wts[0] = small_weights<FMT>(false, a.gu_pair, a.w_gate, a.w_up, a.s_gate, a.s_up, a.d_ff, a.d);
+    p.wts[1] = small_weights<FMT>(false, a.sh_gu_pair, a.sh_gate, a.sh_up, a.sh_s_gate, a.sh_s_up, a.d_ff, a.d);
+    p.in = a.x;
+    p.out = a.h;
+    p.gu_tiles = (int)p.dtiles.d;
     p.gu_rounds = (p.nblocks + kSWaves - 1) / kSWaves;
     p.gu_bytes = (uint32_t)p.nblocks * 2048u * Fmt<FMT>::kVecs;
     hipError_t err;
     if ((err = mark(0)) != hipSuccess) return err;
-    if ((err = launch_projection<FMT, false>(p, stream)) != hipSuccess) return err;
+    if ((err = launch_projection<FMT, false>(p, ws.workers, stream)) != hipSuccess) return err;
     if ((err = mark(1)) != hipSuccess) return err;
-    p.N = a.d;
-    p.K = a.d_ff;
-    p.nblocks = (a.d_ff + kMacroK - 1) / kMacroK;
-    p.tiles = a.d / 32;
-    p.mat_bytes = (uint32_t)packed_matrix_bytes(FMT, a.d, a.d_ff);
-    p.sc_bytes = (uint32_t)packed_scale_bytes(FMT, a.d, a.d_ff);
+
+    geometry(true, a.d, a.d_ff);
+    // MXFP4 scales of the second row tile of an item lie one row tile further.
+    const size_t s1 = FMT == FMT_MXFP4 ? p.sstride / 2 : 0;
+    auto after = [&](const void *s) { return static_cast<const uint8_t *>(s) + s1; };
+    p.wts[0] = small_weights<FMT>(true, a.down_pair, a.w_down, nullptr, a.s_down, after(a.s_down), a.d, a.d_ff);
+    p.wts[1] = small_weights<FMT>(true, a.down_pair, a.sh_down, nullptr, a.sh_s_down, after(a.sh_s_down), a.d, a.d_ff);
+    p.in = a.h;
+    p.out = a.o;
     if ((err = mark(2)) != hipSuccess) return err;
-    if ((err = launch_projection<FMT, true>(p, stream)) != hipSuccess) return err;
+    if ((err = launch_projection<FMT, true>(p, ws.workers, stream)) != hipSuccess) return err;
     if ((err = mark(3)) != hipSuccess) return err;
-    hipLaunchKernelGGL(combine_small_kernel, dim3((a.T * (a.d / 4) + 255) / 256 + 1), dim3(256), 0, stream, p.a);
+    hipLaunchKernelGGL(combine_small_kernel, dim3((a.T * (a.d / 4) + 255) / 256 + 1), dim3(256), 0, stream, a);
     if ((err = hipGetLastError()) != hipSuccess) return err;
     return mark(4);
 }

@@ -165,14 +165,16 @@ constexpr uint32_t kCutBytes = 48u << 10;
 
 struct SmallSplit {
     uint32_t units, per_item;
-    constexpr uint32_t first(uint32_t w, uint32_t G) const { return units * w / G; }
+    constexpr uint32_t first(uint32_t w, uint32_t G) const { return units * w / G; }  // the kernels divide by their Divisor
     // Workgroup holding unit x: the last w with first(w) <= x.
     constexpr uint32_t owner(uint32_t x, uint32_t G) const { return ((x + 1) * G - 1) / units; }
 };
 
-constexpr SmallSplit small_split(uint32_t items, uint32_t rounds, uint32_t item_bytes, uint32_t G)
+// by_G(x): x / G, however the caller divides.
+template <class Div>
+constexpr SmallSplit small_split(uint32_t items, uint32_t rounds, uint32_t item_bytes, uint32_t G, const Div &by_G)
 {
-    const uint32_t idle = (items + G - 1) / G * G - items;  // item-times lost over all workgroups
+    const uint32_t idle = by_G(items + G - 1) * G - items;  // item-times lost over all workgroups
     const bool cut = rounds > 1 && (uint64_t)idle * item_bytes > (uint64_t)G * kCutBytes;
     return cut ? SmallSplit{items * rounds, rounds} : SmallSplit{items, 1u};
 }

@@ -8,7 +8,7 @@ extern "C" {
 unsigned small_split_table(unsigned items, unsigned rounds, unsigned bytes, unsigned G, unsigned *first, unsigned *w0,
                            unsigned *w1)
 {
-    const SmallSplit s = small_split(items, rounds, bytes, G);
+    const SmallSplit s = small_split(items, rounds, bytes, G, [G](unsigned x) { return x / G; });
     for (unsigned w = 0; w <= G; ++w) first[w] = s.first(w, G);
     for (unsigned i = 0; i < items; ++i) {
         w0[i] = s.owner(i * s.per_item, G);
