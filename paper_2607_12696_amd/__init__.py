@@ -70,6 +70,8 @@ _lib = None
 def lib() -> C.CDLL:
     """The loaded library; raises ImportError if it has not been built."""
     global _lib
+    if _lib is not None:
+        return _lib
     with _lock:
         if _lib is None:
             if not os.path.exists(LIB_PATH):
@@ -116,14 +118,25 @@ def _check(fn: str, status: int):
         raise MoeError(fn, status, detail)
 
 
-def _torch():
-    import torch
-    return torch
+_torch_module = None
 
+
+def _torch():
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
+
+
+# The host side of a call is on the critical path of the smallest passes (a GPT-OSS step of one token runs 28 us on
+# the GPU; its Python took 24 us, with 12 us of launches 36 us a step).  So the stream is read as a raw handle
+# (0.1 us; torch.cuda.current_stream builds a Stream object, 1.9 us), the C structs are built by one constructor call,
+# and a routing's integer arrays come from one allocation.
 
 def _stream(t) -> int:
-    torch = _torch()
-    return torch.cuda.current_stream(t.device).cuda_stream
+    """Handle of the current stream of t's device (t is a device tensor)."""
+    return _torch()._C._cuda_getCurrentRawStream(t.get_device())
 
 
 def _dev_ptr(t, what: str) -> int:
@@ -219,22 +232,24 @@ class Routing:
     perm: object
 
     def c_struct(self) -> moe_routing_t:
-        r = moe_routing_t()
-        r.T, r.k, r.E = self.T, self.k, self.E
-        for n in ("topk_idx", "topk_w", "counts", "union_ids", "n_unique", "offsets", "perm"):
-            setattr(r, n, _dev_ptr(getattr(self, n), n))
-        return r
+        return moe_routing_t(self.T, self.k, self.E, _dev_ptr(self.topk_idx, "topk_idx"), _dev_ptr(self.topk_w, "topk_w"),
+                             _dev_ptr(self.counts, "counts"), _dev_ptr(self.union_ids, "union_ids"),
+                             _dev_ptr(self.n_unique, "n_unique"), _dev_ptr(self.offsets, "offsets"),
+                             _dev_ptr(self.perm, "perm"))
+
+
+def _union_arrays(S: int, E: int, device):
+    """Empty int32 counts [E], union_ids [E], n_unique [1], offsets [E + 1], perm [S], from one allocation."""
+    torch = _torch()
+    return torch.empty(3 * E + 2 + S, dtype=torch.int32, device=device).split((E, E, 1, E + 1, S))
 
 
 def moe_expert_union(topk_idx, E: int, topk_w=None, out: Routing | None = None) -> Routing:
     """Expert union, counts, offsets and stable grouping of topk_idx [T, k] on the device."""
-    torch = _torch()
     T, k = topk_idx.shape
     dev = topk_idx.device
     if out is None:
-        i32 = dict(dtype=torch.int32, device=dev)
-        out = Routing(T, k, E, topk_idx, topk_w, torch.empty(E, **i32), torch.empty(E, **i32),
-                      torch.empty(1, **i32), torch.empty(E + 1, **i32), torch.empty(T * k, **i32))
+        out = Routing(T, k, E, topk_idx, topk_w, *_union_arrays(T * k, E, dev))
     _check("moe_expert_union", lib().moe_expert_union(
         _dev_ptr(topk_idx, "topk_idx"), T, k, E, _dev_ptr(out.counts, "counts"), _dev_ptr(out.union_ids, "union_ids"),
         _dev_ptr(out.n_unique, "n_unique"), _dev_ptr(out.offsets, "offsets"), _dev_ptr(out.perm, "perm"),
@@ -245,11 +260,8 @@ def moe_expert_union(topk_idx, E: int, topk_w=None, out: Routing | None = None) 
 def routing_for(topk_idx, topk_w, E: int) -> Routing:
     """A Routing around a top-k (moe_route_topk's output) with empty union and grouping arrays, which
     moe_verify_layer fills."""
-    torch = _torch()
     T, k = topk_idx.shape
-    i32 = dict(dtype=torch.int32, device=topk_idx.device)
-    return Routing(T, k, E, topk_idx, topk_w, torch.empty(E, **i32), torch.empty(E, **i32), torch.empty(1, **i32),
-                   torch.empty(E + 1, **i32), torch.empty(T * k, **i32))
+    return Routing(T, k, E, topk_idx, topk_w, *_union_arrays(T * k, E, topk_idx.device))
 
 
 def moe_route_union(logits, k: int, score: int, out: Routing | None = None) -> Routing:
@@ -260,10 +272,8 @@ def moe_route_union(logits, k: int, score: int, out: Routing | None = None) -> R
         raise ValueError("logits must be float32")
     dev = logits.device
     if out is None:
-        i32 = dict(dtype=torch.int32, device=dev)
-        out = Routing(T, k, E, torch.empty(T, k, **i32), torch.empty(T, k, dtype=torch.float32, device=dev),
-                      torch.empty(E, **i32), torch.empty(E, **i32), torch.empty(1, **i32), torch.empty(E + 1, **i32),
-                      torch.empty(T * k, **i32))
+        out = Routing(T, k, E, torch.empty(T, k, dtype=torch.int32, device=dev),
+                      torch.empty(T, k, dtype=torch.float32, device=dev), *_union_arrays(T * k, E, dev))
     _check("moe_route_union", lib().moe_route_union(
         _dev_ptr(logits, "logits"), T, E, k, score, _dev_ptr(out.topk_idx, "topk_idx"), _dev_ptr(out.topk_w, "topk_w"),
         _dev_ptr(out.counts, "counts"), _dev_ptr(out.union_ids, "union_ids"), _dev_ptr(out.n_unique, "n_unique"),
@@ -361,28 +371,26 @@ def pack_layer(layer: dict, pair: bool = True, down_pair: bool = True) -> dict:
 
 # --------------------------------------------------------------------------- verify layer
 
+_WEIGHT_KEYS = tuple(pre + n for n in ("gate", "up", "down") for pre in ("", "s_", "sh_", "sh_s_"))
+
+
 def weights_struct(w: dict) -> moe_weights_t:
     """moe_weights_t for a layer dict (keys fmt, d, d_ff, E, gate, up, down, optional s_*, sh_*,
     fp32 biases b_gate / b_up [E, d_ff] and b_down [E, d], act / alpha / limit, and act_fmt)."""
-    s = moe_weights_t()
-    torch = _torch()
-    s.act = int(w.get("act", MOE_ACT_SWIGLU))
-    s.act_fmt = int(w.get("act_fmt", MOE_ACTQ_BF16))
-    s.down_paired = int(w.get("down_paired", 0))
-    s.alpha, s.limit = float(w.get("alpha", 1.702)), float(w.get("limit", 7.0))
+    get, f32 = w.get, _torch().float32
+    bias = []
     for name in ("b_gate", "b_up", "b_down"):
-        b = w.get(name)
-        if b is not None and b.dtype != torch.float32:
+        b = get(name)
+        if b is not None and b.dtype != f32:
             raise ValueError(f"{name} must be float32")
-        setattr(s, name, _dev_ptr(b, name))
-    s.fmt, s.d, s.d_ff = int(w["fmt"]), int(w["d"]), int(w["d_ff"])
-    s.E = int(w["E"]) if "E" in w else int(w["gate"].shape[0])
-    for name in ("gate", "up", "down"):
-        setattr(s, "w_" + name, _dev_ptr(w.get(name), name))
-        setattr(s, "s_" + name, _dev_ptr(w.get("s_" + name), "s_" + name))
-        setattr(s, "sh_" + name, _dev_ptr(w.get("sh_" + name), "sh_" + name))
-        setattr(s, "sh_s_" + name, _dev_ptr(w.get("sh_s_" + name), "sh_s_" + name))
-    return s
+        bias.append(_dev_ptr(b, name))
+    E = int(w["E"]) if "E" in w else int(w["gate"].shape[0])
+    p = {n: _dev_ptr(get(n), n) for n in _WEIGHT_KEYS}
+    return moe_weights_t(
+        int(w["fmt"]), int(w["d"]), int(w["d_ff"]), E, p["gate"], p["up"], p["down"], p["s_gate"], p["s_up"], p["s_down"],
+        p["sh_gate"], p["sh_up"], p["sh_down"], p["sh_s_gate"], p["sh_s_up"], p["sh_s_down"], int(get("act", MOE_ACT_SWIGLU)),
+        float(get("alpha", 1.702)), float(get("limit", 7.0)), *bias, int(get("act_fmt", MOE_ACTQ_BF16)),
+        int(get("down_paired", 0)))
 
 
 def moe_verify_workspace_size(weights: dict, T: int, k: int) -> int:
