@@ -69,6 +69,18 @@ __device__ __forceinline__ void load16_lds(const u32x4 &rsrc, uint32_t off, uint
                  : "memory", "m0");
 }
 
+// Brings a kernel's argument struct into the scalar cache with all its lines in flight at once.  Without it
+// each line is fetched where its first field is used, one cold round trip (0.4 us) after the other.
+template <class T>
+__device__ __forceinline__ void fetch_args(const T &args)
+{
+    constexpr int kLine = 16;  // dwords
+    const uint32_t *p = reinterpret_cast<const uint32_t *>(&args);
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(T) / 4); i += kLine) asm volatile("" ::"s"(p[i]));
+    asm volatile("" ::"s"(p[sizeof(T) / 4 - 1]));
+}
+
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 
 // Butterfly reductions over the 64 lanes of a wavefront; every lane gets the result.
@@ -79,36 +91,10 @@ __device__ __forceinline__ float wave_sum(float v)
     return v;
 }
 
-// Maximum of a 64-bit value over the wavefront, with DPP lane moves (row
-// shifts within each row of 16 lanes, then row broadcasts): lane 63 ends with
-// the maximum, which is then read back as a uniform value.  Lanes a move does
-// not reach see 0, the identity of an unsigned maximum.
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ uint64_t dpp_max_step(uint64_t v)
-{
-    const uint32_t lo = __builtin_amdgcn_update_dpp(0u, (uint32_t)v, CTRL, ROW_MASK, 0xf, false);
-    const uint32_t hi = __builtin_amdgcn_update_dpp(0u, (uint32_t)(v >> 32), CTRL, ROW_MASK, 0xf, false);
-    const uint64_t o = ((uint64_t)hi << 32) | lo;
-    return o > v ? o : v;
-}
-
-__device__ __forceinline__ uint64_t wave_max_u64(uint64_t v)
-{
-    v = dpp_max_step<0x111, 0xf>(v);  // row_shr:1
-    v = dpp_max_step<0x112, 0xf>(v);  // row_shr:2
-    v = dpp_max_step<0x114, 0xf>(v);  // row_shr:4
-    v = dpp_max_step<0x118, 0xf>(v);  // row_shr:8: lane 15 of each row holds the row's maximum
-    v = dpp_max_step<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
-    v = dpp_max_step<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3: lane 63 holds the maximum
-    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)v, 63);
-    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(v >> 32), 63);
-    return ((uint64_t)hi << 32) | lo;
-}
-
-// Inclusive sum over lanes 0..lane of a wavefront: the same DPP steps as the
-// maximum above (an inclusive scan within each row of 16 lanes, then the row
-// totals carried into the later rows), a few cycles each, where a ds_bpermute
-// shuffle waits on the LDS crossbar at every step.
+// Inclusive sum over lanes 0..lane of a wavefront, with DPP lane moves (an
+// inclusive scan within each row of 16 lanes, then the row totals carried into
+// the later rows), a few cycles each, where a ds_bpermute shuffle waits on the
+// LDS crossbar at every step.
 template <int CTRL, int ROW_MASK>
 __device__ __forceinline__ int dpp_add_step(int v)
 {

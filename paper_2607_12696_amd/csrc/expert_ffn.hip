@@ -1041,6 +1041,7 @@ void expert_ffn_kernel(FfnParams P)
     constexpr uint32_t BLK = 1024u * NV;  // bytes of one 16 x 128 block of a tile
     __shared__ __attribute__((aligned(16))) uint8_t lds[NT * BBUF];
     const VerifyArgs &a = P.a;
+    fetch_args(P);
     // Workgroups are dispatched round-robin over the 8 XCDs; taking the ranges
     // XCD-major gives each XCD one contiguous eighth of the units, so the
     // workgroups sharing an L2 work on neighbouring items (the same experts'
@@ -1290,6 +1291,7 @@ void expert_ffn_kernel(FfnParams P)
 template <bool DOWN, bool MXA>
 __global__ __launch_bounds__(kThreads) void expert_ffn_fixup_kernel(FfnParams P)
 {
+    fetch_args(P);
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int w = blockIdx.x;
@@ -1401,6 +1403,7 @@ __global__ __launch_bounds__(256) void mx_quant_x_kernel(const uint16_t *__restr
 // plan[8 + 2 * kMaxGroups + u] = first group of expert position u.
 __global__ __launch_bounds__(256) void plan_kernel(VerifyArgs a, int32_t *plan)
 {
+    fetch_args(a);
     __shared__ int wave_tot[256 / kWave];
     const int U = *a.n_unique;
     const int n_exp = U + (a.sh_gate ? 1 : 0);
@@ -1493,6 +1496,7 @@ __device__ __forceinline__ f32x4 expert_out_walk(const FfnParams &D, uint64_t ds
 // common path stays short.
 __global__ __launch_bounds__(256) void combine_kernel(FfnParams D)
 {
+    fetch_args(D);
     constexpr int CH = 8;
     const VerifyArgs &a = D.a;
     const int per_row = a.d / 4;

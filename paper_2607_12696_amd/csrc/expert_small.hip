@@ -129,9 +129,7 @@ void expert_small_kernel(SmallParams P)
     // Distinct experts.
     if (tid < 32) emask[tid] = 0u;
     const int e0 = tid < S ? P.topk_idx[tid] : -1, e1 = tid + kSThreads < S ? P.topk_idx[tid + kSThreads] : -1;
-    // Bring every line of the arguments into the scalar cache now, in the shadow of the slots' load: read
-    // where they are used, each line would cost its own round trip before the first weight load.
-    asm volatile("" ::"s"(P.wts[0].w0), "s"(P.wts[1].w0), "s"(P.wts[1].tstride), "s"(P.in), "s"(P.K), "s"(P.dk.s), "s"(P.limit));
+    fetch_args(P);  // in the shadow of the slots' load
     __syncthreads();
     if (tid < S) sidx[tid] = e0;
     if ((unsigned)e0 < (unsigned)P.E) atomicOr(&emask[e0 >> 5], 1u << (e0 & 31));
@@ -467,6 +465,7 @@ __device__ __forceinline__ void small_union(const VerifyArgs &a)
 // trip.  The last workgroup writes the routing arrays instead.
 __global__ __launch_bounds__(256) void combine_small_kernel(VerifyArgs a)
 {
+    fetch_args(a);
     if (blockIdx.x == gridDim.x - 1) {
         small_union(a);
         return;

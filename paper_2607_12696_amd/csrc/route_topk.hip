@@ -1,14 +1,11 @@
 // Router top-k on gfx950: one 64-lane wavefront per token.
 //
 // Each token's E logits (E <= 1024) are spread over the lanes of one wave.
-// An expert's position in the routing order is a 64-bit key: the upper 32
-// bits map the fp32 logit to an unsigned integer that preserves its order
-// (-0 folded onto +0, NaN below every number) and the lower 32 bits hold the
-// complement of the expert index, so equal logits prefer the lower index and
-// all keys are distinct.  k rounds of a wave-wide max pick the experts in
-// order; the owner lane clears its key after each round.  Gate weights are
-// then a softmax or a renormalised sigmoid over the k selected logits, held
-// one per lane, in fp32.
+// k rounds of a wave-wide maximum over order-preserving 32-bit keys pick the
+// experts in routing order (-0 with +0, NaN below every number, equal logits
+// by the lower index); the winner's key is cleared after each round.  Gate
+// weights are then a softmax or a renormalised sigmoid over the k selected
+// logits, held one per lane, in fp32.
 #include "device.hpp"
 #include "launch.hpp"
 #include "route_common.hpp"
@@ -36,24 +33,45 @@ __global__ __launch_bounds__(256) void route_topk_kernel(const float *__restrict
             val[i] = e < E ? row[e] : 0.f;
         }
     } else {
-        // Sum the slices in order, CH at a time with all their loads in flight.
-        constexpr int CH = EPL >= 8 ? 2 : 8;
+        // Sum the slices in order, a chunk at a time with all its loads in flight: 16 slices up to 4 experts per
+        // lane (a d of 8192 is one round trip), 8 where there are no more.  Loads past the last slice or expert
+        // read zeros, and a chunk has a descriptor of its own, so that its offsets stay below 2^31.
+        const size_t te = (size_t)T * E;
+        constexpr int MOST = EPL <= 4 ? 16 : EPL < 8 ? 8 : 2;
 #pragma unroll
         for (int i = 0; i < EPL; ++i) val[i] = 0.f;
-        for (int s0 = 0; s0 < slices; s0 += CH) {
+        auto add_chunk = [&](int s0, auto width) {
+            constexpr int CH = decltype(width)::value;
+            const rsrc_t rp = make_rsrc(logits + s0 * te, (uint32_t)(min(CH, slices - s0) * te * 4));
             float p[EPL][CH];
 #pragma unroll
+            for (int i = 0; i < EPL; ++i) {
+                const int e = lane + kWave * i;
+                const uint32_t off = e < E ? ((uint32_t)t * (uint32_t)E + (uint32_t)e) * 4u : kOff;
+#pragma unroll
+                for (int c = 0; c < CH; ++c)
+                    p[i][c] = __uint_as_float(
+                        __builtin_amdgcn_raw_buffer_load_b32(rp, (int)(off + (uint32_t)c * (uint32_t)te * 4u), 0, 0));
+            }
+            __builtin_amdgcn_sched_barrier(0);  // keep every load ahead of the first sum
+#pragma unroll
             for (int c = 0; c < CH; ++c)
+#pragma unroll
+                for (int i = 0; i < EPL; ++i) val[i] += p[i][c];  // zeros past the last slice
+        };
+        if (te < (1u << 29) / MOST) {
+            if (MOST == 16 && slices <= 8)
+                add_chunk(0, std::integral_constant<int, 8>{});
+            else
+                for (int s0 = 0; s0 < slices; s0 += MOST) add_chunk(s0, std::integral_constant<int, MOST>{});
+        } else {  // partial sums of 2 GiB and more a chunk: a slice at a time
+#pragma unroll 1
+            for (int c = 0; c < slices; ++c)
 #pragma unroll
                 for (int i = 0; i < EPL; ++i) {
                     const int e = lane + kWave * i;
-                    p[i][c] = (s0 + c < slices && e < E) ? logits[((size_t)(s0 + c) * T + t) * E + e] : 0.f;
+                    if (e < E) val[i] += logits[((size_t)c * T + t) * E + e];
                 }
-#pragma unroll
-            for (int c = 0; c < CH; ++c)
-                if (s0 + c < slices)
-#pragma unroll
-                    for (int i = 0; i < EPL; ++i) val[i] += p[i][c];
         }
         if (logits_out) {
 #pragma unroll
@@ -63,15 +81,12 @@ __global__ __launch_bounds__(256) void route_topk_kernel(const float *__restrict
             }
         }
     }
-    uint64_t key[EPL];
+    uint32_t key[EPL];
 #pragma unroll
-    for (int i = 0; i < EPL; ++i) {
-        const int e = lane + kWave * i;
-        key[i] = e < E ? ((uint64_t)order_key(val[i]) << 32) | (uint32_t)~(uint32_t)e : 0ull;
-    }
-
-    const int mine = select_ranks(key, k);
-    const float wgt = gate_weight(value_of(val, mine), k, score);
+    for (int i = 0; i < EPL; ++i) key[i] = lane + kWave * i < E ? rank_key(val[i]) : 0u;
+    uint32_t mkey;
+    const int mine = select_ranks(key, k, &mkey);
+    const float wgt = gate_weight(key_value(mkey), k, score);
     if (lane < k) {
         topk_idx[(size_t)t * k + lane] = mine;
         topk_w[(size_t)t * k + lane] = wgt;
@@ -81,7 +96,7 @@ __global__ __launch_bounds__(256) void route_topk_kernel(const float *__restrict
 // Group-limited routing (the DeepSeek-V3 rule): sigmoid scores s, choice
 // scores c = s + bias; the E experts form G contiguous groups of gs = E / G
 // (gs >= 2); a group's score is the sum of its two highest choice scores (in
-// the routing order of order_key, so NaN only counts when a group has fewer
+// the routing order of rank_key, so NaN only counts when a group has fewer
 // than two numbers); the TG groups of highest score (ties: lower group) stay
 // eligible and the k highest choice scores among their experts are selected,
 // in order.  Gate weights: scale * s / sum(s) over the selected.  One
@@ -93,59 +108,61 @@ __global__ __launch_bounds__(256) void route_grouped_kernel(const float *__restr
                                                             int G, int TG, float scale, int32_t *__restrict__ topk_idx,
                                                             float *__restrict__ topk_w)
 {
-    __shared__ float cs[4][1024];
+    __shared__ uint32_t cs[4][1024];
     const int lane = lane_id(), wv = threadIdx.x / kWave;
     const int t = blockIdx.x * 4 + wv;
     const bool active = t < T;
     const int gs = E / G;
-    float sv[EPL], cv[EPL];
+    float sv[EPL];
+    uint32_t key[EPL];
 #pragma unroll
     for (int i = 0; i < EPL; ++i) {
         const int e = lane + kWave * i;
         const float l = (active && e < E) ? logits[(size_t)t * E + e] : 0.f;
         sv[i] = 1.f / (1.f + expf(-l));
-        cv[i] = sv[i] + ((bias && e < E) ? bias[e] : 0.f);
-        if (e < E) cs[wv][e] = cv[i];
+        key[i] = rank_key(sv[i] + ((bias && e < E) ? bias[e] : 0.f));
+        if (e < E) cs[wv][e] = key[i];
     }
     __syncthreads();
     if (!active) return;  // uniform per wave, after the block's only barrier
 
-    uint64_t gkey = 0ull;
-    if (lane < G) {
-        uint32_t k1 = 0u, k2 = 0u;
-        float v1 = 0.f, v2 = 0.f;
-        bool h1 = false, h2 = false;
-        for (int j = 0; j < gs; ++j) {
-            const float v = cs[wv][lane * gs + j];
-            const uint32_t kv = order_key(v);
-            if (!h1 || kv > k1) {
-                k2 = k1; v2 = v1; h2 = h1;
-                k1 = kv; v1 = v; h1 = true;
-            } else if (!h2 || kv > k2) {
-                k2 = kv; v2 = v; h2 = true;
-            }
+    // The two highest keys of each group: 1 << sh lanes per group take every (1 << sh)-th expert of it (8 lanes for
+    // 8 groups; one lane a group, walking its 32 experts, took 4 us of the kernel's 12), then merge.
+    const int sh = 31 - __clz(kWave / G);
+    const int grp = lane >> sh, sub = lane & ((1 << sh) - 1);
+    uint32_t k1 = 0u, k2 = 0u;
+    if (grp < G)
+        for (int j = sub; j < gs; j += 1 << sh) {
+            const uint32_t kv = cs[wv][grp * gs + j];
+            k2 = max(k2, min(k1, kv));
+            k1 = max(k1, kv);
         }
-        gkey = ((uint64_t)order_key(v1 + v2) << 32) | (uint32_t)~(uint32_t)lane;
+    for (int m = 1; m < (1 << sh); m <<= 1) {
+        const uint32_t o1 = __shfl_xor(k1, m, kWave), o2 = __shfl_xor(k2, m, kWave);
+        k2 = max(max(k2, o2), min(k1, o1));
+        k1 = max(k1, o1);
     }
+    uint32_t gkey = grp < G && sub == 0 ? rank_key(key_value(k1) + key_value(k2)) : 0u;
     uint64_t gmask = 0ull;  // bit g: group g stays eligible
     for (int r = 0; r < TG; ++r) {
-        const uint64_t m = wave_max_u64(gkey);
-        const int g = (int)~(uint32_t)m;
-        gmask |= 1ull << g;
-        if (lane == g) gkey = 0ull;
+        const uint32_t win = wave_max_u32(gkey);
+        const int first = (int)__builtin_ctzll(__ballot(gkey == win));  // the lowest group of that score
+        gmask |= 1ull << (first >> sh);
+        if (lane == first) gkey = 0u;
     }
-    uint64_t key[EPL];
+    const float inv = 1.f / (float)gs;
 #pragma unroll
     for (int i = 0; i < EPL; ++i) {
         const int e = lane + kWave * i;
-        key[i] = (e < E && ((gmask >> (e / gs)) & 1ull)) ? ((uint64_t)order_key(cv[i]) << 32) | (uint32_t)~(uint32_t)e
-                                                          : 0ull;
+        const int g = (int)(((float)e + 0.5f) * inv);  // e / gs: exact for e < 1024
+        if (!(e < E && ((gmask >> g) & 1ull))) key[i] = 0u;
     }
-    const int mine = select_ranks(key, k);
+    uint32_t mkey;
+    const int mine = select_ranks(key, k, &mkey);
     const bool sel = lane < k;
     const float sm = value_of(sv, mine);  // every lane takes part in the shuffles
     const float g = sel ? sm : 0.f;
-    const float sum = wave_sum(g);
+    const float sum = rank_sum(g, k);
     if (sel) {
         topk_idx[(size_t)t * k + lane] = mine;
         topk_w[(size_t)t * k + lane] = scale * (g / sum);
