@@ -64,6 +64,7 @@
 #include "expert_common.hpp"
 #include "launch.hpp"
 #include "split.hpp"
+#include "union_block.hpp"
 
 // Compile-time tuning: macro steps in flight per wavefront, per format (each
 // the fastest measured: bf16 and MXFP4 steps are 8 KiB per wavefront, MXFP4
@@ -1357,16 +1358,15 @@ __global__ __launch_bounds__(kThreads) void expert_ffn_fixup_kernel(FfnParams P)
     finish_item<DOWN, MXA, 1>(P, d, wave, acc, bias);
 }
 
-// MX activation mode: x [T][K] bf16 -> e4m3fn codes [T][kp] in the FP8
+// MX activation mode: block i of x [T][K] bf16 -> e4m3fn codes [T][kp] in the FP8
 // operand's lane order and e8m0 scales [T][kp / 32] (kp = K padded to a
-// multiple of 128, zeros beyond K), one thread per block of 32 consecutive
-// elements.  Block g of a chunk is K 32g..32g+31; its first 16 codes go to
+// multiple of 128, zeros beyond K), a block being 32 consecutive elements.
+// Block g of a chunk is K 32g..32g+31; its first 16 codes go to
 // chunk byte 64 (g % 2) + 16 (g / 2), its last 16 to 32 bytes further.
-__global__ __launch_bounds__(256) void mx_quant_x_kernel(const uint16_t *__restrict__ x, int T, int K, int kp,
-                                                         uint8_t *__restrict__ xq, uint8_t *__restrict__ xs)
+__device__ __forceinline__ void mx_quant_block(const uint16_t *__restrict__ x, int T, int K, int kp, uint8_t *__restrict__ xq,
+                                               uint8_t *__restrict__ xs, int i)
 {
     const int nb = kp / 32;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= T * nb) return;
     const int row = i / nb, blk = i - row * nb, c = blk >> 2, g = blk & 3;
     float v[32];
@@ -1397,26 +1397,25 @@ __global__ __launch_bounds__(256) void mx_quant_x_kernel(const uint16_t *__restr
     xs[(size_t)row * nb + blk] = (uint8_t)(E + 127);
 }
 
-// Token groups when some expert may have more than 64 tokens (T > 64):
+// Token groups when some expert may have more than 64 tokens (T > 64), by the workgroup that built the union:
 // plan[0] = number of groups; plan[8 + 2i], plan[8 + 2i + 1] = (expert
 // position, group index within the expert) of group i, in expert order;
 // plan[8 + 2 * kMaxGroups + u] = first group of expert position u.
-__global__ __launch_bounds__(256) void plan_kernel(VerifyArgs a, int32_t *plan)
+__device__ __forceinline__ void plan_block(UnionLds &L, const VerifyArgs &a, int32_t *plan)
 {
-    fetch_args(a);
-    __shared__ int wave_tot[256 / kWave];
-    const int U = *a.n_unique;
+    __syncthreads();
+    const int U = L.U, placed = L.placed;
     const int n_exp = U + (a.sh_gate ? 1 : 0);
     int run = 0;
-    for (int base = 0; base < n_exp; base += blockDim.x) {
+    for (int base = 0; base < n_exp; base += kUnionThreads) {
         const int u = base + threadIdx.x;
         int n = 0;
         if (u < n_exp) {
-            const int M = u < U ? a.offsets[u + 1] - a.offsets[u] : a.T;
+            const int M = u < U ? (u + 1 < U ? L.member_start[u + 1] : placed) - L.member_start[u] : a.T;
             n = (M + kTokGroup - 1) / kTokGroup;
         }
         int tot = 0;
-        const int pos = block_exclusive_scan(n, wave_tot, &tot);
+        const int pos = block_exclusive_scan(n, L.wave_tot, &tot);
         if (u < n_exp) plan[8 + 2 * kMaxGroups + u] = run + pos;  // first group of expert position u
         for (int g = 0; g < n; ++g) {
             plan[8 + 2 * (run + pos + g)] = u;
@@ -1425,6 +1424,25 @@ __global__ __launch_bounds__(256) void plan_kernel(VerifyArgs a, int32_t *plan)
         run += tot;
     }
     if (threadIdx.x == 0) plan[0] = run;
+}
+
+constexpr int kQuantThreads = 256;
+
+// What the expert launches of a call need first, in one launch: workgroup 0 builds the union and the token-group
+// plan (T > 64; `grouped`), the others quantise x (MX activations; kpd = 0: none).  As three launches these took
+// 7.5 + 4.6 + 5.7 us (1200 slots, 300 rows of 2880), together 6.8.
+__global__ __launch_bounds__(kUnionThreads) void prepare_kernel(VerifyArgs a, int grouped, int32_t *plan, int kpd)
+{
+    __shared__ UnionLds L;
+    fetch_args(a);
+    if (grouped && blockIdx.x == 0) {
+        union_block(L, a.topk_idx, a.T * a.k, a.E, a.counts, a.union_ids, a.n_unique, a.offsets, a.perm);
+        plan_block(L, a, plan);
+        return;
+    }
+    // A quarter of the threads quantise: more, lighter workgroups (8.8 -> 6.8 us for 300 rows of 2880).
+    if (threadIdx.x < kQuantThreads)
+        mx_quant_block(a.x, a.T, a.d, kpd, a.xq, a.xs, (int)((blockIdx.x - grouped) * kQuantThreads + threadIdx.x));
 }
 
 // A row of a down item cut over two or three ranges (descriptor kind 1): its
@@ -1648,28 +1666,25 @@ static hipError_t launch_fmt(const VerifyArgs &args, uint8_t *ws_base, const Ver
     int32_t *plan = reinterpret_cast<int32_t *>(ws_base + ws.plan_offset);
     hipError_t err;
 
-    if (grouped) {
-        // The token-group plan needs the union first; without it the gate/up kernel builds the union itself.
-        if ((err = launch_expert_union(a.topk_idx, a.T, a.k, a.E, a.counts, a.union_ids, a.n_unique, a.offsets,
-                                       a.perm, stream)) != hipSuccess)
-            return err;
-        hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(256), 0, stream, a, plan);
-        if ((err = hipGetLastError()) != hipSuccess) return err;
-    }
-    if ((err = mark(events, 0, stream)) != hipSuccess) return err;
+    int kpd = 0;
     if constexpr (MXA) {
         auto align = [](size_t v) { return (v + 255) & ~(size_t)255; };
         const size_t rows = (size_t)a.T * a.k + (a.sh_gate ? (size_t)a.T : 0);
-        const int kpd = (a.d + kMacroK - 1) / kMacroK * kMacroK, kpf = (a.d_ff + kMacroK - 1) / kMacroK * kMacroK;
+        const int kpf = (a.d_ff + kMacroK - 1) / kMacroK * kMacroK;
+        kpd = (a.d + kMacroK - 1) / kMacroK * kMacroK;
         a.xq = ws_base + ws.mx_offset;
         a.xs = a.xq + align((size_t)a.T * kpd);
         a.hq = a.xs + align((size_t)a.T * kpd / 32);
         a.hs = a.hq + align(rows * kpf);
-        const int n = a.T * (kpd / 32);
-        hipLaunchKernelGGL(mx_quant_x_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, a.x, a.T, a.d, kpd, a.xq,
-                           a.xs);
+    }
+    if (grouped || MXA) {
+        // The token-group plan needs the union first; without it the gate/up kernel builds the union itself.
+        const int quant = (a.T * (kpd / 32) + kQuantThreads - 1) / kQuantThreads;
+        hipLaunchKernelGGL(prepare_kernel, dim3((grouped ? 1 : 0) + quant), dim3(kUnionThreads), 0, stream, a, grouped ? 1 : 0,
+                           plan, kpd);
         if ((err = hipGetLastError()) != hipSuccess) return err;
     }
+    if ((err = mark(events, 0, stream)) != hipSuccess) return err;
     FfnParams g{};
     g.a = a;
     g.N = a.d_ff;
