@@ -47,7 +47,8 @@ PMC_SUMMARY = {"ds": os.path.join(PROFILES, "expert_ffn_ds_fp8_T64_U32.pmc.txt")
                "gpt": os.path.join(PROFILES, "expert_ffn_gpt_mxfp4_T64_U32.pmc.txt")}
 # The expert kernels' sources: the kernel file and the headers it includes.
 FFN_SOURCES = [os.path.join(ROOT, "paper_2607_12696_amd", "csrc", f)
-               for f in ("expert_ffn.hip", "device.hpp", "launch.hpp", "split.hpp")]
+               for f in ("expert_ffn.hip", "expert_small.hip", "expert_common.hpp", "union_block.hpp", "device.hpp",
+                         "launch.hpp", "split.hpp")]
 GATEUP_FP8 = "expert_ffn_kernel<1, false"   # demangled-name prefix of the FP8 gate/up kernel
 SWEEP_WARMUP = 20                           # untimed steps before each sweep point (the GPU stays busy between points)
 COPY_BYTES = 1 << 30                         # calibration copy: reads and writes 1 GiB
@@ -217,8 +218,8 @@ class Runner:
 
     def step(self, lg, i, events=None):
         """One pass of the hot path: the router top-k, then the verification, which builds the expert
-        union and grouping itself (in the gate/up kernel; T > 64: a union kernel and the token-group plan
-        first).  events = optional 6 marks: before the top-k, then the 5 marks of the timed verify entry
+        union and grouping itself (T <= 16: beside the combine; T <= 64: in the gate/up kernel; beyond: with the
+        token-group plan, first).  events = optional 6 marks: before the top-k, then the 5 marks of the timed verify entry
         point (before and after the gate/up expert kernel, before and after the down expert kernel, after
         combine)."""
         moe, sh = self.moe, self.sh

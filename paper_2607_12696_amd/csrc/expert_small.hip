@@ -19,14 +19,16 @@
 // round-robin instead (a round then reads 32 contiguous KiB) measured the same
 // to 2% slower; rings of half or twice the depth are no faster.
 //
-// Split.  The items of a launch (expert-major) are cut into equal contiguous
-// ranges, one per workgroup, in closed form from the number of distinct
-// experts alone: no cost prefix, no search, no schedule.  Ranges normally hold
-// whole items.  Where whole items would leave the workgroups idle for long
-// (few, large items) the gate/up ranges are cut at rounds instead; the pieces
-// of a cut item stay in the workspace as fp32 sums and the down launch adds
-// them, in workgroup order, as it loads its activations, finding them with the
-// same closed form.  There is no fix-up launch.
+// Split.  The items of a launch (expert-major) are cut into contiguous ranges
+// of whole items, one per workgroup, in closed form from the number of distinct
+// experts alone: no cost prefix, no search, no schedule, no sums across
+// workgroups and so no fix-up launch.  A range is at most one item longer than
+// another; the workgroups still streaming then share the bandwidth of the idle
+// ones.  Cutting gate/up items at K blocks where that idle time looked long,
+// with the pieces added by the down launch, was slower wherever it applied:
+// Qwen T = 4 on 13 experts 83.6 -> 88.6 us, one Qwen expert (96 items on 256
+// workgroups) 22.8 -> 32.9 us.  Cutting down items between their two row tiles
+// gained nothing either (GPT-OSS T = 16 on 16 experts 50.8 -> 51.8 us).
 //
 // H and O rows sit at the routed slots (t * k + j; the shared expert's at
 // T * k + t).  A launch needs no grouping: the distinct experts are a bit set
@@ -35,20 +37,18 @@
 // of the combine launch, beside the others.
 //
 // Measured against the general kernels (whole pass, same box): GPT-OSS layer
-// T = 1 47.1 -> 33.7 us, T = 4 (8-layer graph, with its router) 594 -> 466 us;
-// Qwen layer T = 4, 13 experts 105.6 -> 91.3 us; DeepSeek layer T = 4,
-// 31 experts 236.9 -> 231.5 us, T = 16, 37 experts 324 -> 309 us.  At T = 16 each
-// further expert streams at 6.4 (FP8), 6.5 (bf16) and 6.7 TB/s (MXFP4; 6.3
-// before); what is left above the stream is 22 us a pass (35 to 40 before).
+// T = 1 47.3 -> 27.9 us (with a leaner host call), T = 4 (8-layer graph, with its
+// router) 592 -> 427 us; Qwen layer T = 4 108.9 -> 89.2 us; DeepSeek layer T = 4 on
+// 31 experts 236.2 -> 228.1 us, T = 16 330 -> 307 us.  At T = 16 each further
+// expert streams at 6.4 (FP8), 6.5 (bf16) and 6.7 TB/s (MXFP4; 6.3 before); what
+// is left above the stream is about 20 us a pass (35 to 40 before).
 #include "expert_common.hpp"
-#include "split.hpp"
 
 namespace ecospec {
 
 constexpr int kSWaves = 8;
 constexpr int kSThreads = kSWaves * kWave;
 constexpr int kSmallSlots = kSmallT * 64;  // routed slots: k <= 64
-constexpr int kPieceFloats = 2 * kWave * 4;  // partial sums of one piece of a cut item (gate and up tile)
 
 // A divisor known before the launch: x / d for x < 2^31 as a multiplication (the 31-bit case of the
 // round-up method: m = ceil(2^(31 + s) / d) with s = ceil(log2 d) fits 32 bits and is exact).
@@ -77,14 +77,11 @@ struct SmallParams {
     const int32_t *topk_idx;
     const void *in;        // x or H
     void *out;             // H or O
-    float *pieces;         // [workers][2][kPieceFloats]
     const float *b_gate, *b_up;
     int T, k, S, E, U_extra;  // U_extra: 1 with a shared expert
     int K, nblocks, ldo;      // reduction length, its 128-wide blocks, columns of a row of `out`
     uint32_t sc_bytes, sstride;  // bytes of an expert's scales; MXFP4: of one item's
     Divisor dG, dtiles, dk;   // workgroups, items per expert, top-k
-    int gu_tiles, gu_rounds;  // the gate/up launch's items per expert and rounds per item
-    uint32_t gu_bytes;        // and bytes per item
     int act;
     float alpha, limit;
 };
@@ -95,12 +92,12 @@ template <int FMT> struct SmallSlot {
     uint32_t sc[2];  // FP8: the block scales' bits; MXFP4: the lane's e8m0 codes of a quad of blocks
 };
 
-// Prefetch ring: D rounds in flight per wavefront.  An item is J rounds, padded to JU so that the loop
+// Prefetch ring: D rounds in flight per wavefront (bf16 rounds are 8 KiB: two measured 1 to 10% faster than four).  An item is J rounds, padded to JU so that the loop
 // (P items unrolled) is a whole number of turns of the ring; J blocks of activations (16 registers each)
 // and D slots share the 256 registers of a wavefront (the down kernels need a few more than gate/up).
 template <int FMT, bool DOWN, int J> struct Ring {
-    static constexpr int D = FMT == FMT_FP8    ? (DOWN && J >= 6 ? 2 : J == 3 || J == 5 || J == 6 ? J : 4)
-                           : FMT == FMT_BF16   ? (J == 1 || J == 3 || J == 5 || J == 6 ? 3 : J >= 7 ? 2 : 4)
+    static constexpr int D = FMT == FMT_FP8    ? (J >= 7 || (DOWN && J == 6) ? 2 : J == 6 ? 3 : J == 3 || J == 5 ? J : 4)
+                           : FMT == FMT_BF16   ? (J == 1 || J == 3 || J == 5 || J == 6 ? 3 : 2)
                                                : (J <= 3 ? 6 : J == 4 ? 8 : J <= 6 ? J : 4);
     static constexpr int JU = J >= D ? (J + D - 1) / D * D : J;
     static constexpr int P = JU >= D ? 1 : D / JU;
@@ -153,22 +150,13 @@ void expert_small_kernel(SmallParams P)
         return 32 * wl + (int)__builtin_ctzll(hit);
     };
 
-    const split::SmallSplit gs = split::small_split(n_exp * (uint32_t)P.gu_tiles, (uint32_t)P.gu_rounds, P.gu_bytes, G, P.dG);
-    const split::SmallSplit sp = DOWN ? split::SmallSplit{n_exp * P.dtiles.d, 1u} : gs;
-    const uint32_t x0 = P.dG(sp.units * w), x1 = P.dG(sp.units * (w + 1));
+    const uint32_t items = n_exp * P.dtiles.d;  // items * (G + 1) < 2^31
+    const uint32_t x0 = P.dG(items * w), x1 = P.dG(items * (w + 1));
     if (x0 >= x1) return;
-    uint32_t t0 = x0, tl = x1 - 1;
-    int jfirst = 0, jlast = J;  // first round of the first item, end round of the last item
-    if (sp.per_item != 1) {
-        t0 = x0 / sp.per_item;
-        tl = (x1 - 1) / sp.per_item;
-        jfirst = (int)(x0 - t0 * sp.per_item);
-        jlast = (int)(x1 - tl * sp.per_item);
-    }
-    const int n = (int)(tl - t0) + 1;  // items of the range
+    const int n = (int)(x1 - x0);  // items of the range
     const int nkb = P.nblocks, tiles = (int)P.dtiles.d;
     const int kb0 = nkb * wave / kSWaves, kcount = nkb * (wave + 1) / kSWaves - kb0;  // this wavefront's K blocks
-    const int u0 = (int)P.dtiles(t0), it0 = (int)t0 - u0 * tiles;
+    const int u0 = (int)P.dtiles(x0), it0 = (int)x0 - u0 * tiles;
 
     // Load cursor: the item whose weights are being issued.  Offsets are scalar: a load's address is its
     // descriptor's base + wj + the lane's 16 bytes.  A dead load (past the range, or a block another
@@ -190,7 +178,7 @@ void expert_small_kernel(SmallParams P)
         }
     };
     set_expert(u0);
-    int ci = 0, ct = it0, cu = u0, jlo = jfirst, jhi = min(n == 1 ? jlast : J, kcount);
+    int ci = 0, ct = it0, cu = u0, jhi = kcount;
     uint32_t wj = (uint32_t)ct * tstride + (uint32_t)kb0 * kstride;
     auto advance = [&]() {
         ++ci;
@@ -198,15 +186,16 @@ void expert_small_kernel(SmallParams P)
             ct = 0;
             if (ci < n) set_expert(++cu);
         }
-        jlo = 0;
-        jhi = ci < n ? min(ci == n - 1 ? jlast : J, kcount) : 0;
+        jhi = ci < n ? kcount : 0;
         wj = (uint32_t)ct * tstride + (uint32_t)kb0 * kstride;
     };
 
     SmallSlot<FMT> ring[D];
     const uint32_t lane16 = (uint32_t)lane * 16u, lane4 = (uint32_t)lane * 4u;
     auto issue = [&](int slot, int j) {
-        const bool live = j >= jlo && j < jhi;
+        int h = jhi;
+        asm volatile("" : "+s"(h));  // not an invariant to be kept in vector registers for every j
+        const bool live = j < h;
         const uint32_t dead = live ? 0u : kOff, vo = lane16 | dead;
         const int wo = live ? (int)wj : 0;
 #pragma unroll
@@ -260,50 +249,6 @@ void expert_small_kernel(SmallParams P)
             for (int s = 0; s < 4; ++s)
                 bx[j][s] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rb, (int)(vo + 16u * s), so, 0));
         }
-        if (DOWN && gs.per_item > 1) {
-            // H columns of gate/up items that were cut between workgroups: add their pieces.  A rolled loop:
-            // the code is cold and few items are cut (at most one per workgroup boundary).
-#pragma unroll 1
-            for (int h = 0; h < 2 * J; ++h) {
-                const int n0 = (kb0 + h / 2) * kMacroK + 32 * grp + 16 * (h & 1);  // this lane's 16 columns
-                const uint32_t ib = ((uint32_t)u * (uint32_t)P.gu_tiles + (uint32_t)(n0 / 16)) * gs.per_item;
-                const bool in = h / 2 < kcount && n0 < P.K;
-                const uint32_t w0 = in ? gs.owner(ib, G) : 0u, w1 = in ? gs.owner(ib + gs.per_item - 1, G) : 0u;
-                if (w0 == w1) continue;
-                f32x4 g[4], up[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const size_t o = (size_t)ce * P.K + n0 + 4 * q;
-                    g[q] = ce >= 0 && P.b_gate ? *reinterpret_cast<const f32x4 *>(P.b_gate + o) : f32x4{0.f, 0.f, 0.f, 0.f};
-                    up[q] = ce >= 0 && P.b_up ? *reinterpret_cast<const f32x4 *>(P.b_up + o) : f32x4{0.f, 0.f, 0.f, 0.f};
-                }
-                for (uint32_t v = w0; v <= w1; ++v) {
-                    const uint32_t f = P.dG(gs.units * v);
-                    if (f >= P.dG(gs.units * (v + 1))) continue;  // a workgroup without units
-                    const float *src = P.pieces + ((size_t)v * 2 + split::small_piece(f, ib)) * kPieceFloats + col * 4;
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        g[q] += *reinterpret_cast<const f32x4 *>(src + 64 * q);
-                        up[q] += *reinterpret_cast<const f32x4 *>(src + kPieceFloats / 2 + 64 * q);
-                    }
-                }
-                u32x4 pk[2];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    float v[4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) v[i] = activate(P.act, P.alpha, P.limit, g[q][i], up[q][i]);
-                    pk[q >> 1][2 * (q & 1)] = pack_bf16x2(v[0], v[1]);
-                    pk[q >> 1][2 * (q & 1) + 1] = pack_bf16x2(v[2], v[3]);
-                }
-#pragma unroll
-                for (int hh = 0; hh < 2 * J; ++hh)
-                    if (hh == h && myslot >= 0) {
-                        bx[hh / 2][2 * (hh & 1)] = __builtin_bit_cast(bf16x8, pk[0]);
-                        bx[hh / 2][2 * (hh & 1) + 1] = __builtin_bit_cast(bf16x8, pk[1]);
-                    }
-            }
-        }
     };
 
     // Pipeline prologue: the first item's weights, the activations, then the rest of the ring.
@@ -327,13 +272,17 @@ void expert_small_kernel(SmallParams P)
                 if (P.b_up) ub = *reinterpret_cast<const f32x4 *>(P.b_up + o);
             }
             f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
-            const int jl = i == 0 ? jfirst : 0, jh = i == n - 1 ? jlast : J;
+            const int live_rounds = i < n ? kcount : 0;
 #pragma unroll
             for (int j = 0; j < JU; ++j) {
                 const int q = p * JU + j + D - 1;  // the round whose loads go out now
                 if (q % JU == 0) advance();
                 issue(q % D, q % JU);
-                if (j < J && i < n && j >= jl && j < jh) {
+                // A branch per round, on a value opaque to the compiler: without it, it interleaves the rounds'
+                // decoding and spills (FP8, J = 7: 18 registers; DeepSeek T = 4 227 -> 248 us).
+                int jlive = live_rounds;
+                asm volatile("" : "+s"(jlive));
+                if (j < jlive) {
                     const SmallSlot<FMT> &sl = ring[(p * JU + j) % D];
 #pragma unroll
                     for (int t = 0; t < 2; ++t) {
@@ -373,20 +322,14 @@ void expert_small_kernel(SmallParams P)
                             *reinterpret_cast<f32x4 *>(dst) = r0;
                             *reinterpret_cast<f32x4 *>(dst + 16) = r1;
                         }
-                    } else if (jl == 0 && jh == J) {
-                        if (myslot >= 0) {
-                            r0 += gb;
-                            r1 += ub;
-                            float h[4];
+                    } else if (myslot >= 0) {
+                        r0 += gb;
+                        r1 += ub;
+                        float h[4];
 #pragma unroll
-                            for (int r = 0; r < 4; ++r) h[r] = activate(P.act, P.alpha, P.limit, r0[r], r1[r]);
-                            *reinterpret_cast<u32x2 *>(static_cast<uint16_t *>(P.out) + (size_t)myslot * P.ldo + 16 * bt + 4 * grp) =
-                                u32x2{pack_bf16x2(h[0], h[1]), pack_bf16x2(h[2], h[3])};
-                        }
-                    } else {
-                        float *dst = P.pieces + ((size_t)w * 2 + (jl > 0 ? 0 : 1)) * kPieceFloats + lane * 4;
-                        *reinterpret_cast<f32x4 *>(dst) = r0;
-                        *reinterpret_cast<f32x4 *>(dst + kPieceFloats / 2) = r1;
+                        for (int r = 0; r < 4; ++r) h[r] = activate(P.act, P.alpha, P.limit, r0[r], r1[r]);
+                        *reinterpret_cast<u32x2 *>(static_cast<uint16_t *>(P.out) + (size_t)myslot * P.ldo + 16 * bt + 4 * grp) =
+                            u32x2{pack_bf16x2(h[0], h[1]), pack_bf16x2(h[2], h[3])};
                     }
                 }
                 if (++bt == tiles) {
@@ -525,8 +468,8 @@ bool small_verify(const VerifyArgs &a, int workers)
     if (a.T > kSmallT || a.act_fmt != 0 || nu > 8 * kSWaves || nd > 8 * kSWaves) return false;
     // The split's arithmetic is 32-bit.
     const uint64_t n_exp = (uint64_t)(a.E < a.T * a.k ? a.E : a.T * a.k) + 1;
-    const uint64_t units = n_exp * ((uint64_t)(a.d_ff / 16) * ((nu + kSWaves - 1) / kSWaves) + a.d / 32);
-    return units * ((uint64_t)workers + 1) < (1ull << 31);
+    const uint64_t items = n_exp * (uint64_t)(a.d_ff / 16 > a.d / 32 ? a.d_ff / 16 : a.d / 32);
+    return items * ((uint64_t)workers + 1) < (1ull << 31);
 }
 
 // The weights of the routed or of the shared expert for one launch: `w` (and, unpaired gate/up, `w2`).
@@ -560,7 +503,6 @@ static hipError_t launch_small_fmt(const VerifyArgs &args, uint8_t *ws_base, con
     a.o = reinterpret_cast<float *>(ws_base + ws.o_offset);
     SmallParams p{};
     p.topk_idx = a.topk_idx;
-    p.pieces = reinterpret_cast<float *>(ws_base + ws.p_offset);
     p.b_gate = a.b_gate;
     p.b_up = a.b_up;
     p.T = a.T;
@@ -587,9 +529,6 @@ static hipError_t launch_small_fmt(const VerifyArgs &args, uint8_t *ws_base, con
     p.wts[1] = small_weights<FMT>(false, a.sh_gu_pair, a.sh_gate, a.sh_up, a.sh_s_gate, a.sh_s_up, a.d_ff, a.d);
     p.in = a.x;
     p.out = a.h;
-    p.gu_tiles = (int)p.dtiles.d;
-    p.gu_rounds = (p.nblocks + kSWaves - 1) / kSWaves;
-    p.gu_bytes = (uint32_t)p.nblocks * 2048u * Fmt<FMT>::kVecs;
     hipError_t err;
     if ((err = mark(0)) != hipSuccess) return err;
     if ((err = launch_projection<FMT, false>(p, ws.workers, stream)) != hipSuccess) return err;

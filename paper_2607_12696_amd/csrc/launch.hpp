@@ -39,8 +39,8 @@ struct VerifyArgs {
     int act;             // 0: SwiGLU, 1: GPT-OSS clamped SwiGLU
     float alpha, limit;
     const float *b_gate, *b_up, *b_down;  // routed experts' biases or null
-    // The union and grouping of the slots (Eq. 1): written by the call itself (by the gate/up kernel, or by
-    // the union kernel when T > 64), read by its later kernels.
+    // The union and grouping of the slots (Eq. 1): written by the call itself (T <= 16: by the combine kernel;
+    // T <= 64: by the gate/up kernel, for its later kernels; beyond: by the launch before it).
     int32_t *counts, *union_ids, *n_unique, *offsets, *perm;
     const uint16_t *x;  // [T][d] bf16
     uint16_t *y;        // [T][d] bf16

@@ -153,35 +153,5 @@ constexpr int packed_slot(long long code, int i) { return (int)((code >> (20 * i
 constexpr int first_worker(long long code) { return (int)(code >> 16) & 0xffff; }
 constexpr int last_worker(long long code) { return (int)code & 0xffff; }
 
-// The closed-form split of small calls (T <= 16, where every item of a launch
-// costs the same): unit = one item, or one round (a K block per wavefront) of an item
-// where whole items would leave workgroups idle for more than kCutBytes of
-// streaming.  Workgroup w of G takes the units [first(w), first(w + 1)).
-// 32-bit throughout: units * G < 2^31 (checked by the launcher).
-//
-// The line: a cut costs the down launch a round trip per expert to add the
-// pieces (about 2 us, i.e. 50 KB of a workgroup's streaming).
-constexpr uint32_t kCutBytes = 48u << 10;
-
-struct SmallSplit {
-    uint32_t units, per_item;
-    constexpr uint32_t first(uint32_t w, uint32_t G) const { return units * w / G; }  // the kernels divide by their Divisor
-    // Workgroup holding unit x: the last w with first(w) <= x.
-    constexpr uint32_t owner(uint32_t x, uint32_t G) const { return ((x + 1) * G - 1) / units; }
-};
-
-// by_G(x): x / G, however the caller divides.
-template <class Div>
-constexpr SmallSplit small_split(uint32_t items, uint32_t rounds, uint32_t item_bytes, uint32_t G, const Div &by_G)
-{
-    const uint32_t idle = by_G(items + G - 1) * G - items;  // item-times lost over all workgroups
-    const bool cut = rounds > 1 && (uint64_t)idle * item_bytes > (uint64_t)G * kCutBytes;
-    return cut ? SmallSplit{items * rounds, rounds} : SmallSplit{items, 1u};
-}
-
-// Which of a workgroup's two piece slots holds its piece of the item starting at unit ib, f being the
-// workgroup's first unit: 0 if its range starts inside the item, else 1.
-constexpr uint32_t small_piece(uint32_t f, uint32_t ib) { return f > ib ? 0u : 1u; }
-
 }  // namespace split
 }  // namespace ecospec

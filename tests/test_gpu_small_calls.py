@@ -1,7 +1,6 @@
 """Verification passes of at most 16 tokens (their own kernels) against the CPU oracle, at the sizes where the
 kernels' K blocks per wavefront, their tails and their split change: 1 to 8 rounds of eight 128-wide blocks in both
-projections, ragged last blocks, items cut between workgroups (few large items) and whole, both packings, biases,
-a shared expert, and 17 tokens or more than 64 blocks, which the general kernels take."""
+projections, ragged last blocks, fewer items than workgroups, both packings, biases, a shared expert, and 17 tokens or more than 64 blocks, which the general kernels take."""
 import numpy as np
 import pytest
 import torch
@@ -71,11 +70,10 @@ def test_tokens_options_and_packings(T, fmt, shared, oai, pair):
     check(fmt, 384, 640, T, E=7, k=3, shared=shared, oai=oai, pair=pair, rows=T)
 
 
-# Few large items: gate/up items cut at rounds between workgroups (a bf16 item of d = 4096 is 256 KiB).  One expert
-# of 96 items spreads each over up to three workgroups; T = 16 puts every column of the pieces to use.
+# Few large items: fewer than workgroups (one expert of 96 or 10 items), or little more than a range each.
 @pytest.mark.parametrize("fmt,d,d_ff,E,oai", [(0, 4096, 1536, 1, False), (0, 8192, 1024, 1, True), (0, 4096, 160, 2, False),
-                                              (1, 7168, 512, 3, True), (2, 8192, 512, 1, True)])
-def test_items_cut_between_workgroups(fmt, d, d_ff, E, oai):
+                                              (1, 7168, 512, 3, True), (2, 8192, 512, 1, True), (1, 128, 4224, 1, False)])
+def test_few_large_items(fmt, d, d_ff, E, oai):
     check(fmt, d, d_ff, 16, E=E, k=1, shared=fmt == 1, oai=oai)
 
 
