@@ -1,6 +1,4 @@
-// Grouped SwiGLU experts of the verification pass on gfx950 (CDNA4): the general
-// kernels, for more than 16 tokens, MX activations and the longest reductions
-// (other calls: expert_small.hip).
+// Grouped SwiGLU experts of the verification pass on gfx950 (CDNA4).
 //
 // The pass is bound by HBM bandwidth: every distinct expert routed to by the
 // verified tokens must be read once, while each weight serves only the M_u
