@@ -1,5 +1,6 @@
 // The verification pass of small calls (T <= 16 tokens) on gfx950: every
-// expert serves at most one 16-token block.
+// expert serves at most one 16-token block, unless tokens name it more than once
+// (rows padded with zeros do).
 //
 // These calls are bound by the weight stream and by the latency of its
 // launches, so the kernels differ from the general ones (expert_ffn.hip) in
@@ -32,7 +33,9 @@
 //
 // H and O rows sit at the routed slots (t * k + j; the shared expert's at
 // T * k + t).  A launch needs no grouping: the distinct experts are a bit set
-// in LDS and an expert's slots are found with ballots.  The routing arrays of
+// in LDS and an expert's slots are found with ballots.  An expert of more than
+// 16 slots takes part once more for each further 16 (`extra`, built only if one
+// of the slots' counts says so).  The routing arrays of
 // the caller (counts, union, offsets, perm) are written by one extra workgroup
 // of the combine launch, beside the others.
 //
@@ -113,6 +116,9 @@ void expert_small_kernel(SmallParams P)
     using R = Ring<FMT, DOWN, J>;
     constexpr int D = R::D, JU = R::JU, PU = R::P;
     __shared__ uint32_t emask[32];                // distinct routed experts (E <= 1024)
+    __shared__ int cnt[1024];                     // slots of each expert
+    __shared__ int extra[kSmallSlots / kSmallT];  // expert | first slot << 16 of each block of slots past an expert's first
+    __shared__ int n_extra;                       // their number; -1: to be counted
     __shared__ int sidx[kSmallSlots];             // expert of each routed slot
     __shared__ int slots[kSWaves][kSmallT];       // slots of the current expert (one copy per wavefront)
     __shared__ f32x4 red[2][kSWaves][2][kWave];   // an item's partial sums, double-buffered
@@ -125,22 +131,42 @@ void expert_small_kernel(SmallParams P)
 
     // Distinct experts.
     if (tid < 32) emask[tid] = 0u;
+    cnt[tid] = cnt[tid + kSThreads] = 0;
+    if (tid == 0) n_extra = 0;
     const int e0 = tid < S ? P.topk_idx[tid] : -1, e1 = tid + kSThreads < S ? P.topk_idx[tid + kSThreads] : -1;
     fetch_args(P);  // in the shadow of the slots' load
     __syncthreads();
-    if (tid < S) sidx[tid] = e0;
-    if ((unsigned)e0 < (unsigned)P.E) atomicOr(&emask[e0 >> 5], 1u << (e0 & 31));
-    if (S > kSThreads) {
-        if (tid + kSThreads < S) sidx[tid + kSThreads] = e1;
-        if ((unsigned)e1 < (unsigned)P.E) atomicOr(&emask[e1 >> 5], 1u << (e1 & 31));
-    }
+    auto enter = [&](int slot, int e) {
+        if (slot < S) sidx[slot] = e;
+        if ((unsigned)e < (unsigned)P.E) {
+            atomicOr(&emask[e >> 5], 1u << (e & 31));
+            if (S > kSmallT && atomicAdd(&cnt[e], 1) >= kSmallT) n_extra = -1;
+        }
+    };
+    enter(tid, e0);
+    if (S > kSThreads) enter(tid + kSThreads, e1);
     __syncthreads();
+    if (n_extra < 0) {
+        __syncthreads();
+        if (wave == 0) {
+            int n = 0;
+            for (int e = lane; e < 1024; e += kWave) {
+                const int more = (max(cnt[e], 1) - 1) / kSmallT, incl = wave_inclusive_sum(more);
+                for (int b = 0; b < more; ++b) extra[n + incl - more + b] = e | (kSmallT * (b + 1)) << 16;
+                n += __builtin_amdgcn_readlane(incl, 63);
+            }
+            if (lane == 0) n_extra = n;
+        }
+        __syncthreads();
+    }
     const uint32_t mword = lane < 32 ? emask[lane] : 0u;
     const int mcount = __popc(mword), mincl = wave_inclusive_sum(mcount);
     const int U = __builtin_amdgcn_readlane(mincl, 63);
-    const uint32_t n_exp = (uint32_t)(U + P.U_extra);
-    // Id of the u-th distinct expert (wave-uniform; -1: the shared expert).
+    const int n_first = U + P.U_extra;
+    const uint32_t n_exp = (uint32_t)(n_first + __builtin_amdgcn_readfirstlane(n_extra));
+    // Id of the u-th expert: the distinct ones, the shared expert (-1), then those of `extra` (wave-uniform).
     auto expert_of = [&](int u) -> int {
+        if (u >= n_first) return __builtin_amdgcn_readfirstlane(extra[u - n_first]) & 0xffff;
         if (u >= U) return -1;
         const int wl = __builtin_ctzll(__ballot(mincl > u && mincl - mcount <= u));
         const uint32_t word = __builtin_amdgcn_readlane(mword, wl);
@@ -227,12 +253,13 @@ void expert_small_kernel(SmallParams P)
         if (ce < 0) {
             myslot = col < P.T ? S + col : -1;
         } else {
-            int cnt = 0;
+            const int skip = u >= n_first ? __builtin_amdgcn_readfirstlane(extra[u - n_first]) >> 16 : 0;
+            int cnt = -skip;
             for (int base = 0; base < S; base += kWave) {
                 const bool hit = base + lane < S && sidx[base + lane] == ce;
                 const uint64_t m = __ballot(hit);
                 const int r = cnt + __popcll(m & ((1ull << lane) - 1ull));
-                if (hit && r < kSmallT) slots[wave][r] = base + lane;
+                if (hit && (unsigned)r < (unsigned)kSmallT) slots[wave][r] = base + lane;
                 cnt += __popcll(m);
             }
             __builtin_amdgcn_wave_barrier();  // the same wavefront's LDS accesses stay in order
@@ -467,7 +494,7 @@ bool small_verify(const VerifyArgs &a, int workers)
     const int nu = (a.d + kMacroK - 1) / kMacroK, nd = (a.d_ff + kMacroK - 1) / kMacroK;
     if (a.T > kSmallT || a.act_fmt != 0 || nu > 8 * kSWaves || nd > 8 * kSWaves) return false;
     // The split's arithmetic is 32-bit.
-    const uint64_t n_exp = (uint64_t)(a.E < a.T * a.k ? a.E : a.T * a.k) + 1;
+    const uint64_t n_exp = (uint64_t)(a.E < a.T * a.k ? a.E : a.T * a.k) + 1 + a.T * a.k / kSmallT;
     const uint64_t items = n_exp * (uint64_t)(a.d_ff / 16 > a.d / 32 ? a.d_ff / 16 : a.d / 32);
     return items * ((uint64_t)workers + 1) < (1ull << 31);
 }
