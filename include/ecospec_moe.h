@@ -300,7 +300,10 @@ moe_status_t moe_verify_workspace_size(const moe_weights_t *w, int T, int k, siz
  *   y[t] = sum_j topk_w[t][j] * FFN_{topk_idx[t][j]}(x[t])  (+ FFN_shared(x[t]))
  *   FFN_e(x) = W_down[e] (silu(W_gate[e] x) * (W_up[e] x))
  * Each distinct routed expert (and the shared one) is streamed from HBM once
- * per call for up to 64 of its tokens (once per 64 tokens beyond that).
+ * per call for up to 64 of its tokens (once per 64 tokens beyond that).  A
+ * token may name an expert more than once: every slot counts, and where an
+ * expert so gets more slots than T, it is streamed once per T of them (T
+ * rounded up to a multiple of 16, at most 64).
  *   x  [T][d] bf16 in, y [T][d] bf16 out (may not alias x), device.
  *   r  routing for the same T, k, E: topk_idx and topk_w in (moe_route_topk);
  *      counts, union_ids, n_unique, offsets and perm out, the union of the

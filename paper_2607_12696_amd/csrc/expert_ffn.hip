@@ -89,6 +89,7 @@ namespace ecospec {
 
 constexpr int kMB = 4;                  // 16-token blocks per item
 constexpr int kTokGroup = 16 * kMB;     // tokens per item
+static_assert(kTokGroup == split::kGroupRows);
 // An item's rows are cut into kWG slots: 16 rows (gate/up, with the same
 // rows of the up matrix) or 32 rows (down) each.  Slots are the unit of the
 // partial-sum layout and of the fix-up kernel (one wavefront per slot); an
@@ -103,12 +104,9 @@ constexpr int kEThreads = kPW * kWave;               // expert kernels
 constexpr int kBRowsPerPass = kEThreads / 16;        // activation rows staged per pass (16 threads per row)
 constexpr int kBPass = kTokGroup / kBRowsPerPass;    // passes per step
 static_assert(kWG % kPW == 0, "whole slots per wavefront");
-// Floats of one partial-sum slot: a workgroup's accumulators of the live token
-// blocks (a token group holds at most min(T, 64) tokens).
-constexpr int partial_floats(int T)
-{
-    return kWG * 2 * 4 * kWave * (((T < kTokGroup ? T : kTokGroup) + 15) / 16);
-}
+// Floats of one partial-sum slot: a workgroup's accumulators of the token
+// blocks a group can have.
+constexpr int partial_floats(int T) { return kWG * 2 * 4 * kWave * (split::group_rows(T) / 16); }
 
 // Wave-uniform loads through the constant address space (scalar memory).
 __device__ __forceinline__ int ld_s(const int32_t *p)
@@ -203,7 +201,7 @@ struct FfnParams {
     int slot_floats;      // floats per partial-sum slot: partial_floats(T)
     long long *ranges;    // [workers][2]: unit range [x0, x1) of each workgroup, written by the expert kernel
     long long *fix;       // gate/up only: [workers][4] fix-up record of each workgroup (see write_fix_record)
-    const int32_t *plan;  // token groups when T > 64 (else null: one group per expert)
+    const int32_t *plan;  // token groups when T > 64 (else null: union_and_costs() makes them)
     void *dn_sched;       // T <= 64: the down launch's schedule (DownSched), written by the gate/up launch
     int dn_K;             // gate/up: the down launch's units per token group (bands x steps)
 };
@@ -212,14 +210,6 @@ struct FfnParams {
 struct Plan {
     int U, n_groups;
 };
-
-__device__ __forceinline__ Plan load_plan(const FfnParams &P)
-{
-    Plan pl;
-    pl.U = ld_s(P.a.n_unique);
-    pl.n_groups = P.plan ? ld_s(P.plan) : pl.U + (P.a.sh_gate ? 1 : 0);
-    return pl;
-}
 
 // ----------------------------------------------------------------------------- cost-weighted split
 //
@@ -278,57 +268,28 @@ struct Split {
     int wave_tot[2 * kWG];
 };
 
-// Fills sp.cw and the groups' metadata for the launch (whole workgroup) and
-// returns the plan.  Without a token-group plan (one group per union member,
-// then the shared expert) the union's offsets and ids are read for every
-// possible member in the same round trip as the union size and the slots'
-// tokens: the schedule waits for global memory once, not twice.
+// Fills sp.cw and the groups' metadata from the token-group plan (whole
+// workgroup) and returns the plan.
 template <int FMT, bool MXA, bool DOWN>
 __device__ __forceinline__ Plan build_costs(const FfnParams &P, Split &sp)
 {
-    constexpr int kPre = (1024 + kEThreads - 1) / kEThreads;  // groups per thread read ahead (E <= 1024: every union)
     const VerifyArgs &a = P.a;
     const int S = a.T * a.k;
     const int tid = threadIdx.x;
-    int o0[kPre], o1[kPre], id[kPre];
-#pragma unroll
-    for (int j = 0; j < kPre; ++j) {
-        const int g = j * kEThreads + tid;
-        const bool ok = P.plan == nullptr && g < a.E;
-        o0[j] = ok ? a.offsets[g] : 0;
-        o1[j] = ok ? a.offsets[g + 1] : 0;
-        id[j] = ok ? a.union_ids[g] : 0;
-    }
-    const Plan pl = load_plan(P);
+    const Plan pl{ld_s(a.n_unique), ld_s(P.plan)};
     if (S <= kMaxTokLds)
         for (int p = tid; p < S; p += kEThreads) sp.tok[p] = DOWN ? a.perm[p] : a.perm[p] / a.k;
     int run = 0;
-    for (int base = 0, j = 0; base < pl.n_groups; base += kEThreads, ++j) {
+    for (int base = 0; base < pl.n_groups; base += kEThreads) {
         const int g = base + tid;
         int c = 0;
         if (g < pl.n_groups) {
-            const int u = P.plan ? P.plan[8 + 2 * g] : g, tg = P.plan ? P.plan[8 + 2 * g + 1] : 0;
+            const int u = P.plan[8 + 2 * g], tg = P.plan[8 + 2 * g + 1];
             const bool shared = u >= pl.U;
-            int lo = 0, hi = 0, e = -1;
-            if (!shared) {
-                if (P.plan == nullptr && j < kPre) {
-#pragma unroll
-                    for (int q = 0; q < kPre; ++q)
-                        if (q == j) {
-                            lo = o0[q];
-                            hi = o1[q];
-                            e = id[q];
-                        }
-                } else {
-                    lo = a.offsets[u];
-                    hi = a.offsets[u + 1];
-                    e = a.union_ids[u];
-                }
-            }
-            const int Mu = shared ? a.T : hi - lo;
+            const int lo = shared ? S : a.offsets[u], Mu = shared ? a.T : a.offsets[u + 1] - lo;
             sp.gM[g] = min(kTokGroup, Mu - tg * kTokGroup);
-            sp.gp0[g] = (shared ? S : lo) + tg * kTokGroup;
-            sp.ge[g] = e;
+            sp.gp0[g] = lo + tg * kTokGroup;
+            sp.ge[g] = shared ? -1 : a.union_ids[u];
             c = group_cost<FMT, MXA>(sp.gM[g]);
         }
         int tot = 0;
@@ -341,8 +302,8 @@ __device__ __forceinline__ Plan build_costs(const FfnParams &P, Split &sp)
     return pl;
 }
 
-// Gate/up launch without a token-group plan (T <= 64: every expert's tokens
-// form one group).  The union of the routed experts and the grouping of the
+// Gate/up launch without a token-group plan (T <= 64: every expert's slots
+// form one group, or several if tokens name it more than once).  The union of the routed experts and the grouping of the
 // slots by expert (Eq. 1, the stable counting sort moe_expert_union computes)
 // are built by each workgroup in LDS straight from topk_idx, with the groups'
 // costs; workgroup 0 also writes them to the routing arrays for the later
@@ -394,9 +355,9 @@ __device__ __forceinline__ Plan union_and_costs(const FfnParams &P, Split &sp, i
         }
         if (ps + 1 < passes) __syncthreads();  // one pass: its counts stay in wcnt for the placement
     }
-    // Union positions, first grouped positions and the cost prefix.  A group
-    // keeps at most 64 tokens (more only with repeated experts within a token).
-    int run_u = 0, run_p = 0, run_c = 0, start[EPT];
+    // Union positions, groups, first grouped positions and the cost prefix.
+    const int rows = split::group_rows(a.T), full = group_cost<FMT, MXA>(rows);
+    int run_u = 0, run_g = 0, run_p = 0, run_c = 0, start[EPT];
 #pragma unroll
     for (int j = 0; j < EPT; ++j) start[j] = 0;
 #pragma unroll
@@ -404,34 +365,43 @@ __device__ __forceinline__ Plan union_and_costs(const FfnParams &P, Split &sp, i
         if (j >= nj) break;
         const int e = j * kEThreads + tid;
         const int c = e < E ? tot[j] : 0;
-        const int M = min(kTokGroup, c);
+        const int extra = split::extra_groups(c, rows);
         int up, cp, tup, tcost;
-        block_exclusive_scan2((c << 11) | (c > 0 ? 1 : 0), c > 0 ? group_cost<FMT, MXA>(M) : 0, sp.wave_tot, up, cp,
-                              tup, tcost);
-        const int pos = run_u + (up & 2047);
-        start[j] = run_p + (up >> 11);
+        block_exclusive_scan2(split::pack_member(c, extra),
+                              c > 0 ? extra * full + group_cost<FMT, MXA>(c - extra * rows) : 0, sp.wave_tot, up, cp, tup,
+                              tcost);
+        const int pos = run_u + split::member_used(up);
+        start[j] = run_p + split::member_slots(up);
         if (c > 0) {
-            sp.ge[pos] = e;
-            sp.gp0[pos] = start[j];
-            sp.gM[pos] = M;
-            sp.cw[pos] = run_c + cp;
+            const int g = run_g + split::member_used(up) + split::member_extra(up);
+            for (int i = 0; i <= extra; ++i) {
+                sp.ge[g + i] = e;
+                sp.gp0[g + i] = start[j] + i * rows;
+                sp.gM[g + i] = min(rows, c - i * rows);
+                sp.cw[g + i] = run_c + cp + i * full;
+            }
+            if (out) {
+                a.union_ids[pos] = e;
+                a.offsets[pos] = start[j];
+            }
         }
         if (out && e < E) a.counts[e] = c;
-        run_u += tup & 2047;
-        run_p += tup >> 11;
+        run_u += split::member_used(tup);
+        run_g += split::member_used(tup) + split::member_extra(tup);
+        run_p += split::member_slots(tup);
         run_c += tcost;
     }
     Plan pl;
     pl.U = run_u;
-    pl.n_groups = run_u + (a.sh_gate ? 1 : 0);
+    pl.n_groups = run_g + (a.sh_gate ? 1 : 0);
     if (tid == 0) {
         int total = run_c;
         if (a.sh_gate) {  // the shared expert: all T tokens, after every routed slot
-            sp.ge[run_u] = -1;
-            sp.gp0[run_u] = S;
-            sp.gM[run_u] = min(kTokGroup, a.T);
-            sp.cw[run_u] = run_c;
-            total += group_cost<FMT, MXA>(min(kTokGroup, a.T));
+            sp.ge[run_g] = -1;
+            sp.gp0[run_g] = S;
+            sp.gM[run_g] = a.T;
+            sp.cw[run_g] = run_c;
+            total += full;
         }
         sp.cw[pl.n_groups] = total;
     }
@@ -472,9 +442,9 @@ __device__ __forceinline__ Plan union_and_costs(const FfnParams &P, Split &sp, i
         if (ps + 1 < passes) __syncthreads();
     }
     if (out) {
-        for (int u = tid; u <= E; u += kEThreads) {
-            if (u < E) a.union_ids[u] = u < run_u ? sp.ge[u] : -1;
-            a.offsets[u] = u < run_u ? sp.gp0[u] : run_p;
+        for (int u = run_u + tid; u <= E; u += kEThreads) {
+            if (u < E) a.union_ids[u] = -1;
+            a.offsets[u] = run_p;
         }
         if (tid == 0) *a.n_unique = run_u;
     }
@@ -502,13 +472,14 @@ __device__ __forceinline__ int owner_of(const Split &sp, int n_groups, long K, i
     return split::owner_of(sp.cw, n_groups, K, W, x);
 }
 
-// The down launch's schedule when every expert's tokens form one group (T <= 64): its token
-// groups are the gate/up launch's (the union members in order, then the shared expert) with the
+// The down launch's schedule without a token-group plan (T <= 64): its token
+// groups are the gate/up launch's (the union members' in order, then the shared expert's) with the
 // same costs, so only the unit ranges differ (K is the down launch's).  Workgroup 0 of the gate/up
 // launch, which also writes the union, writes it before its first weight load; the down launch
 // then reads it in one round trip instead of rebuilding it from the union.
-constexpr int kSchedGroups = 1025;  // n_groups <= E + 1, E <= 1024
+constexpr int kSchedGroups = split::kMaxCallGroups;
 struct DownSched {
+    int n_groups;
     long long bound[kMaxWorkers + 1];
     int cw[kSchedGroups + 1], ge[kSchedGroups], gp0[kSchedGroups], gM[kSchedGroups];
 };
@@ -516,6 +487,7 @@ struct DownSched {
 __device__ __forceinline__ void write_down_sched(const FfnParams &P, const Plan &pl, const Split &sp)
 {
     DownSched *ds = static_cast<DownSched *>(P.dn_sched);
+    if (threadIdx.x == 0) ds->n_groups = pl.n_groups;
     const long K = P.dn_K;
     const long long C = (long long)sp.cw[pl.n_groups] * K;
     for (int v = threadIdx.x; v <= P.workers; v += kEThreads)
@@ -556,7 +528,7 @@ __device__ __forceinline__ Plan load_down_sched(const FfnParams &P, Split &sp)
         gp0[j] = ok && g < kSchedGroups ? ds->gp0[g] : 0;
         gM[j] = ok && g < kSchedGroups ? ds->gM[g] : 0;
     }
-    const Plan pl = load_plan(P);
+    const Plan pl{ld_s(P.a.n_unique), ld_s(&ds->n_groups)};
     if (S <= kMaxTokLds)
         for (int p = tid; p < S; p += kEThreads) sp.tok[p] = a.perm[p];
 #pragma unroll
@@ -1733,7 +1705,7 @@ static hipError_t launch_fmt(const VerifyArgs &args, uint8_t *ws_base, const Ver
     hipLaunchKernelGGL((expert_ffn_kernel<FMT, false, PD, MXA>), dim3(G), dim3(kEThreads), 0, stream, g);
     if ((err = hipGetLastError()) != hipSuccess) return err;
     if ((err = mark(events, 1, stream)) != hipSuccess) return err;
-    const int token_blocks = ((a.T < kTokGroup ? a.T : kTokGroup) + 15) / 16;
+    const int token_blocks = split::group_rows(a.T) / 16;
     hipLaunchKernelGGL((expert_ffn_fixup_kernel<MXA>), dim3(G, token_blocks), dim3(kThreads), 0, stream, g);
     if ((err = hipGetLastError()) != hipSuccess) return err;
 

@@ -35,6 +35,32 @@ constexpr long long div_floor(long long a, long long b)
     return q;
 }
 
+// Token groups.  An expert's slots form groups of at most group_rows(T) rows:
+// min(T, 64) in whole 16-token blocks, which is what a partial-sum slot of the
+// call holds.  One group per expert serves a call of up to 64 tokens, unless
+// tokens name an expert more than once.
+constexpr int kGroupRows = 64;
+constexpr int group_rows(int T) { return ((T < kGroupRows ? T : kGroupRows) + 15) / 16 * 16; }
+
+// Groups past the first of an expert with c > 0 slots (no division: there are none as a rule).
+constexpr int extra_groups(int c, int rows)
+{
+    int n = 0;
+    for (c -= rows; c > 0; c -= rows) ++n;
+    return n;
+}
+
+// Most groups of a call of up to 64 tokens, 64 slots each, on up to 1024 experts and a shared one: each expert's
+// first, and one per group_rows(T) of the 64 T - 1024 slots past them (most at T = 64), or, up to 16 tokens, one a slot.
+constexpr int kMaxCallGroups = 1024 + (64 * 64 - 1024) / 64 + 1;
+
+// What union_and_costs() scans over the experts in one word: slots (up to 4096), groups past the first (up to 63)
+// and used experts (up to 1024).
+constexpr int pack_member(int c, int extra) { return (c << 17) | (extra << 11) | (c > 0 ? 1 : 0); }
+constexpr int member_slots(int v) { return v >> 17; }
+constexpr int member_extra(int v) { return (v >> 11) & 63; }
+constexpr int member_used(int v) { return v & 2047; }
+
 // First unit x with P_x * W >= target (0 <= target <= C*K*W); n_groups*K if none.
 constexpr long first_unit(const int *cw, int n_groups, long K, long W, long long target)
 {

@@ -35,4 +35,15 @@ void split_out_fields(unsigned long long code, int *f)
     f[8] = out_w1(code);
     f[9] = out_tail0(code);
 }
+int split_group_rows(int T) { return group_rows(T); }
+int split_extra_groups(int c, int rows) { return extra_groups(c, rows); }
+int split_max_call_groups() { return kMaxCallGroups; }
+int split_pack_member(int c, int extra) { return pack_member(c, extra); }
+// Fields of a (sum of) packed members: slots, extra groups, used experts.
+void split_member_fields(int v, int *f)
+{
+    f[0] = member_slots(v);
+    f[1] = member_extra(v);
+    f[2] = member_used(v);
+}
 }

@@ -83,3 +83,28 @@ def test_small_calls(kind, T, k, fmt, d, d_ff, shared, oai):
 @pytest.mark.parametrize("kind", KINDS)
 def test_small_calls_of_1024_slots(kind):
     check(kind, 0, 64, 64, 16, 64, E=64)
+
+
+# The general kernels: 17 to 64 tokens, where an expert's slots may need several token groups and nearly every item is
+# cut between workgroups; MX activations and more than 64 K blocks at any T; and the token-group plan beyond 64.
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("T,k", [(17, 2), (17, 7), (32, 5), (33, 7), (48, 7), (49, 1), (64, 2), (64, 7), (70, 3)])
+@pytest.mark.parametrize("fmt,d,d_ff,shared,oai", LAYERS)
+def test_general_calls(kind, T, k, fmt, d, d_ff, shared, oai):
+    check(kind, fmt, d, d_ff, T, k, shared=shared, oai=oai)
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("T,k", [(1, 7), (3, 7), (16, 7), (33, 7), (64, 3), (70, 3)])
+def test_mx_calls(kind, T, k):
+    check(kind, 2, 160, 320, T, k, shared=True, mx=True)
+
+
+@pytest.mark.parametrize("kind", KINDS)
+def test_long_reductions(kind):
+    check(kind, 0, 8224, 64, 3, 7)
+
+
+@pytest.mark.parametrize("kind", KINDS)
+def test_general_calls_of_4096_slots(kind):
+    check(kind, 0, 64, 64, 64, 64, E=64)

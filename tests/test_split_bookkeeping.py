@@ -290,3 +290,31 @@ def test_first_unit_at_large_magnitudes(lib):
                 want = (g + 1) * K if r >= K else g * K + r
             got = lib.split_first_unit(cw.ctypes.data, n, K, W, target)
             assert got == want, (n, K, W, w)
+
+
+def test_token_groups_of_calls_up_to_64_tokens(lib):
+    """An expert's slots in groups of at most group_rows(T) rows (what a partial-sum slot holds), however often tokens
+    name it: the groups cover the slots, their number stays within the down schedule's, and the scan's packed word
+    holds every prefix."""
+    rng = np.random.default_rng(5)
+    f = (C.c_int * 3)()
+    most = lib.split_max_call_groups()
+    for T in range(1, 65):
+        rows = lib.split_group_rows(T)
+        assert rows % 16 == 0 and T <= rows <= 64 and rows - T < 16
+        for k in (1, 2, 7, 8, 32, 63, 64):
+            S = T * k
+            draws = [np.array([S])]  # every slot on one expert
+            for U in {1, min(S, 2), min(S, 1024)}:  # U experts, one of them with every slot left over
+                draws.append(np.array([1] * (U - 1) + [S - U + 1]))
+            for _ in range(3):
+                draws.append(np.bincount(rng.integers(0, int(rng.integers(1, 1025)), S), minlength=1024))
+            for counts in draws:
+                extra = [lib.split_extra_groups(int(c), rows) for c in counts]
+                for c, x in zip(counts.tolist(), extra):
+                    assert (x == 0 if c == 0 else x * rows < c <= (x + 1) * rows)
+                members = sum(lib.split_pack_member(int(c), x) for c, x in zip(counts, extra))
+                assert members < 2 ** 31
+                lib.split_member_fields(members, f)
+                assert list(f) == [S, sum(extra), int((counts > 0).sum())]
+                assert f[1] + f[2] + 1 <= most  # and the shared expert's group
