@@ -10,12 +10,13 @@
 // Items.  An item is one 16-row tile of W_gate with the same tile of W_up, or
 // 32 rows of W_down, over the whole reduction.  Its 128-wide K blocks are
 // divided over the workgroup's eight wavefronts (an eighth of the reduction
-// each, taken in J rounds of one block), so an item is one contiguous run of
-// memory and every wavefront keeps the same K blocks from item to item.  The
+// each, taken in J rounds of one block; short reductions over fewer, with
+// several items side by side: waves_per_item), so an item is one contiguous run
+// of memory and every wavefront keeps the same K blocks from item to item.  The
 // activations those blocks need (16 tokens x 128 elements each) therefore stay
 // in registers, as matrix-core operands, for all items of an expert: no
-// activation tiles, and no barrier per step.  The eight partial sums of an
-// item are added through LDS, in wavefront order, by one wavefront (a
+// activation tiles, and no barrier per step.  The partial sums of an item are
+// added through LDS, in wavefront order, by one wavefront (a
 // different one each item), behind the item's one barrier.  Dealing the blocks
 // round-robin instead (a round then reads 32 contiguous KiB) measured the same
 // to 2% slower; rings of half or twice the depth are no faster.
@@ -107,10 +108,12 @@ template <int FMT, bool DOWN, int J> struct Ring {
     static_assert((P * JU) % D == 0 && JU >= J, "whole turns of the ring");
 };
 
-template <int FMT, bool DOWN, int J>
+// KW: wavefronts that share an item; the workgroup takes kSWaves / KW items at a time (a turn).
+template <int FMT, bool DOWN, int J, int KW>
 __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void expert_small_kernel(SmallParams P)
 {
+    constexpr int NC = kSWaves / KW;
     constexpr int NV = Fmt<FMT>::kVecs;
     constexpr uint32_t BLK = 1024u * NV;
     using R = Ring<FMT, DOWN, J>;
@@ -127,6 +130,7 @@ void expert_small_kernel(SmallParams P)
     const uint32_t w = G % 8 == 0 ? (blockIdx.x % 8) * (G / 8) + blockIdx.x / 8 : blockIdx.x;
     const int tid = threadIdx.x, lane = lane_id(), col = lane & 15, grp = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int sub = NC == 1 ? 0 : wave / KW, part = NC == 1 ? wave : wave % KW;
     const int S = P.S;
 
     // Distinct experts.
@@ -181,8 +185,21 @@ void expert_small_kernel(SmallParams P)
     if (x0 >= x1) return;
     const int n = (int)(x1 - x0);  // items of the range
     const int nkb = P.nblocks, tiles = (int)P.dtiles.d;
-    const int kb0 = nkb * wave / kSWaves, kcount = nkb * (wave + 1) / kSWaves - kb0;  // this wavefront's K blocks
-    const int u0 = (int)P.dtiles(x0), it0 = (int)x0 - u0 * tiles;
+    const int kb0 = nkb * part / KW, kcount = nkb * (part + 1) / KW - kb0;  // this wavefront's K blocks
+    const int mine_n = sub < n ? (n - sub + NC - 1) / NC : 0;               // its items: x0 + sub, x0 + sub + NC, ...
+    const uint32_t xs = x0 + (sub < n ? sub : 0);
+    const int u0 = (int)P.dtiles(xs), it0 = (int)xs - u0 * tiles;
+
+    // The wavefront's next item: its tile and expert; whether the expert is another.
+    auto step = [&](int &t, int &u) {
+        t += NC;
+        if (t < tiles) return false;
+        do {
+            t -= tiles;
+            ++u;
+        } while (NC > 1 && t >= tiles);
+        return true;
+    };
 
     // Load cursor: the item whose weights are being issued.  Offsets are scalar: a load's address is its
     // descriptor's base + wj + the lane's 16 bytes.  A dead load (past the range, or a block another
@@ -204,15 +221,12 @@ void expert_small_kernel(SmallParams P)
         }
     };
     set_expert(u0);
-    int ci = 0, ct = it0, cu = u0, jhi = kcount;
+    int ci = 0, ct = it0, cu = u0, jhi = NC == 1 || mine_n > 0 ? kcount : 0;
     uint32_t wj = (uint32_t)ct * tstride + (uint32_t)kb0 * kstride;
     auto advance = [&]() {
         ++ci;
-        if (++ct == tiles) {
-            ct = 0;
-            if (ci < n) set_expert(++cu);
-        }
-        jhi = ci < n ? kcount : 0;
+        if (step(ct, cu) && ci < mine_n) set_expert(cu);
+        jhi = ci < mine_n ? kcount : 0;
         wj = (uint32_t)ct * tstride + (uint32_t)kb0 * kstride;
     };
 
@@ -284,22 +298,23 @@ void expert_small_kernel(SmallParams P)
     for (int q = 0; q < D - 1; ++q) {
         if (q > 0 && q % JU == 0) advance();
         issue(q, q % JU);
-        if (q == (J < D - 1 ? J : D - 1) - 1) load_b(bu);
+        if (q == (J < D - 1 ? J : D - 1) - 1 && (NC == 1 || mine_n > 0)) load_b(bu);
     }
     const bool biased = !DOWN && (P.b_gate != nullptr || P.b_up != nullptr);
-    for (int i0 = 0; i0 < n; i0 += PU) {
+    const int turns = (n + NC - 1) / NC;
+    for (int i0 = 0; i0 < turns; i0 += PU) {
 #pragma unroll
         for (int p = 0; p < PU; ++p) {
             const int i = i0 + p;
-            const bool mine = wave == (i & (kSWaves - 1));  // this wavefront finishes the item
+            const bool mine = part == (i & (KW - 1));  // this wavefront finishes the item
             f32x4 gb = f32x4{0.f, 0.f, 0.f, 0.f}, ub = gb;
-            if (biased && mine && i < n && ce >= 0) {
+            if (biased && mine && i < mine_n && ce >= 0) {
                 const size_t o = (size_t)ce * P.ldo + 16 * bt + 4 * grp;
                 if (P.b_gate) gb = *reinterpret_cast<const f32x4 *>(P.b_gate + o);
                 if (P.b_up) ub = *reinterpret_cast<const f32x4 *>(P.b_up + o);
             }
             f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
-            const int live_rounds = i < n ? kcount : 0;
+            const int live_rounds = i < mine_n ? kcount : 0;
 #pragma unroll
             for (int j = 0; j < JU; ++j) {
                 const int q = p * JU + j + D - 1;  // the round whose loads go out now
@@ -329,19 +344,25 @@ void expert_small_kernel(SmallParams P)
                     }
                 }
             }
-            if (i < n) {
+            if (i < turns) {
                 const int buf = i & 1;
-                red[buf][wave][0][lane] = acc[0];
-                red[buf][wave][1][lane] = acc[1];
-                // LDS only: the weight loads in flight stay in flight.  An item's sums are read before the
-                // next item's barrier and overwritten after it.
-                asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-                if (mine) {
-                    f32x4 r0 = red[buf][0][0][lane], r1 = red[buf][0][1][lane];
+                if constexpr (KW > 1) {
+                    red[buf][wave][0][lane] = acc[0];
+                    red[buf][wave][1][lane] = acc[1];
+                    // LDS only: the weight loads in flight stay in flight.  A turn's sums are read before the
+                    // next turn's barrier and overwritten after it.
+                    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+                }
+                if (mine && (NC == 1 || i < mine_n)) {
+                    f32x4 r0 = acc[0], r1 = acc[1];
+                    if constexpr (KW > 1) {
+                        r0 = red[buf][sub * KW][0][lane];
+                        r1 = red[buf][sub * KW][1][lane];
 #pragma unroll
-                    for (int v = 1; v < kSWaves; ++v) {
-                        r0 += red[buf][v][0][lane];
-                        r1 += red[buf][v][1][lane];
+                        for (int v = 1; v < KW; ++v) {
+                            r0 += red[buf][sub * KW + v][0][lane];
+                            r1 += red[buf][sub * KW + v][1][lane];
+                        }
                     }
                     if (DOWN) {
                         if (myslot >= 0) {
@@ -359,10 +380,7 @@ void expert_small_kernel(SmallParams P)
                             u32x2{pack_bf16x2(h[0], h[1]), pack_bf16x2(h[2], h[3])};
                     }
                 }
-                if (++bt == tiles) {
-                    bt = 0;
-                    if (i + 1 < n) load_b(++bu);
-                }
+                if (step(bt, bu) && i + 1 < mine_n) load_b(bu);
             }
         }
     }
@@ -473,16 +491,25 @@ __global__ __launch_bounds__(256) void combine_small_kernel(VerifyArgs a)
 
 // ----------------------------------------------------------------------------- host side
 
+// Wavefronts that share an item: eight, or for short reductions the fewest that leave each at most two rounds.  With
+// eight throughout, reductions of up to eight blocks left wavefronts without a block and paid the item's barrier for
+// a few KiB, at least 0.7 us per item: 128 experts of 128 x 8192 (T = 16) took 235 us in bf16, 204 in FP8 and 191 in MXFP4
+// (the general kernels 141, 100 and 106), now 134, 72 and 54; 640 x 2176 in MXFP4 85 (general 83), now 65; 2048 x 768 in
+// MXFP4 74 (general 71), now 66.
+static int waves_per_item(int nblocks) { return nblocks <= 2 ? 1 : nblocks <= 4 ? 2 : nblocks <= 8 ? 4 : kSWaves; }
+
 template <int FMT, bool DOWN>
 static hipError_t launch_projection(const SmallParams &p, int workers, hipStream_t stream)
 {
     const dim3 grid(workers), block(kSThreads);
-    switch ((p.nblocks + kSWaves - 1) / kSWaves) {
-#define SMALL_CASE(J)                                                                          \
-    case J:                                                                                    \
-        hipLaunchKernelGGL((expert_small_kernel<FMT, DOWN, J>), grid, block, 0, stream, p);    \
+    const int kw = waves_per_item(p.nblocks), rounds = (p.nblocks + kw - 1) / kw;
+    switch (kw * 16 + rounds) {
+#define SMALL_CASE(KW, J)                                                                          \
+    case KW * 16 + J:                                                                              \
+        hipLaunchKernelGGL((expert_small_kernel<FMT, DOWN, J, KW>), grid, block, 0, stream, p);    \
         break;
-        SMALL_CASE(1) SMALL_CASE(2) SMALL_CASE(3) SMALL_CASE(4) SMALL_CASE(5) SMALL_CASE(6) SMALL_CASE(7) SMALL_CASE(8)
+        SMALL_CASE(1, 1) SMALL_CASE(1, 2) SMALL_CASE(2, 2) SMALL_CASE(4, 2) SMALL_CASE(8, 2) SMALL_CASE(8, 3)
+        SMALL_CASE(8, 4) SMALL_CASE(8, 5) SMALL_CASE(8, 6) SMALL_CASE(8, 7) SMALL_CASE(8, 8)
 #undef SMALL_CASE
     default: return hipErrorInvalidValue;
     }

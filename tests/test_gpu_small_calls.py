@@ -79,3 +79,13 @@ def test_few_large_items(fmt, d, d_ff, E, oai):
 
 def test_many_slots_per_token():
     check(synth.FMT_BF16, 64, 64, 16, E=1024, k=64, rows=16)
+
+
+# Reductions of 1 to 8 blocks, whose items 1, 2 or 4 wavefronts share: 8, 4 or 2 items side by side.  Experts of a
+# single item (32 x 32) put several experts side by side; with 40 experts some workgroups get a last, partial turn.
+@pytest.mark.parametrize("fmt,d,d_ff", [(0, 32, 32), (2, 32, 32), (0, 288, 544), (2, 288, 544), (0, 480, 800), (2, 480, 800),
+                                        (0, 1024, 640), (2, 1024, 640), (0, 160, 1152), (2, 3072, 96), (1, 128, 128), (1, 384, 512),
+                                        (1, 640, 256), (1, 768, 896), (1, 1024, 128), (1, 128, 3072)])
+@pytest.mark.parametrize("T,E,k", [(1, 5, 1), (16, 40, 8)])
+def test_short_reductions(fmt, d, d_ff, T, E, k):
+    check(fmt, d, d_ff, T, E=E, k=k, shared=True, oai=fmt == 2, pair=d != d_ff)
