@@ -96,13 +96,22 @@ template <int FMT> struct SmallSlot {
     uint32_t sc[2];  // FP8: the block scales' bits; MXFP4: the lane's e8m0 codes of a quad of blocks
 };
 
-// Prefetch ring: D rounds in flight per wavefront (bf16 rounds are 8 KiB: two measured 1 to 10% faster than four).  An item is J rounds, padded to JU so that the loop
-// (P items unrolled) is a whole number of turns of the ring; J blocks of activations (16 registers each)
-// and D slots share the 256 registers of a wavefront (the down kernels need a few more than gate/up).
-template <int FMT, bool DOWN, int J> struct Ring {
-    static constexpr int D = FMT == FMT_FP8    ? (J >= 7 || (DOWN && J == 6) ? 2 : J == 6 ? 3 : J == 3 || J == 5 ? J : 4)
-                           : FMT == FMT_BF16   ? (J == 1 || J == 3 || J == 5 || J == 6 ? 3 : 2)
-                                               : (J <= 3 ? 6 : J == 4 ? 8 : J <= 6 ? J : 4);
+// Prefetch ring: D rounds in flight per wavefront.  An item is J rounds, padded to JU so that the loop (P items
+// unrolled) is a whole number of turns of the ring; J blocks of activations (16 registers each) and D slots (FP8 16
+// registers, bf16 32, MXFP4 10) share the 256 registers of a wavefront.  Up to two rounds an item, D is what keeps P
+// at one or a few: each unrolled item is a copy of the epilogue, and the copies cost more than the depth brings (32
+// experts, T = 4: 128 x 4096 FP8 4 -> 2 rounds 19.8 -> 17.7 us, MXFP4 6 -> 3 19.3 -> 17.7; 2048 x 2048 MXFP4 6 -> 4 47.4 ->
+// 45.8).  FP8 keeps four where eight wavefronts share 9 to 16 blocks: with nine, most of them have one block, so that
+// two rounds hold one live one (128 experts of 1152 x 1152, T = 16: 90.8 us with four, 94.8 with two; with all 16 blocks
+// two are 2% faster).  Beyond that the depth matters little, so these are J itself or a divisor where the
+// registers hold it: FP8 with two rounds throughout is 0.6 and 1.0% slower at J = 3 and 4, 1.1 and 0.6% faster at 5 and
+// 6; MXFP4 with three or four is 1.4% slower, 1.2% faster, 3.0% and 0.4% slower at J = 3 to 6; bf16 with two instead of three
+// is within 0.2% at J = 5 and 6 and 1.3% faster at 3, with three instead of two 3.8% faster at 4 (4096 x 4096) and 2% slower
+// for Qwen's J = 4 and 2.  J = 7 padded to eight rounds and not padded (P = 2) are the same (DeepSeek T = 4 213.8, 213.9 us).
+template <int FMT, bool DOWN, int J, int KW> struct Ring {
+    static constexpr int D = FMT == FMT_FP8    ? (J <= 2 ? (KW < kSWaves ? 2 : 4) : J >= 7 || (DOWN && J == 6) ? 2 : J == 6 ? 3 : J)
+                           : FMT == FMT_BF16   ? (J == 3 || J == 5 || J == 6 ? 3 : 2)
+                                               : (J == 1 ? 3 : J == 3 ? 6 : J == 4 ? 8 : J == 5 || J == 6 ? J : 4);
     static constexpr int JU = J >= D ? (J + D - 1) / D * D : J;
     static constexpr int P = JU >= D ? 1 : D / JU;
     static_assert((P * JU) % D == 0 && JU >= J, "whole turns of the ring");
@@ -116,7 +125,7 @@ void expert_small_kernel(SmallParams P)
     constexpr int NC = kSWaves / KW;
     constexpr int NV = Fmt<FMT>::kVecs;
     constexpr uint32_t BLK = 1024u * NV;
-    using R = Ring<FMT, DOWN, J>;
+    using R = Ring<FMT, DOWN, J, KW>;
     constexpr int D = R::D, JU = R::JU, PU = R::P;
     __shared__ uint32_t emask[32];                // distinct routed experts (E <= 1024)
     __shared__ int cnt[1024];                     // slots of each expert
@@ -186,19 +195,27 @@ void expert_small_kernel(SmallParams P)
     const int n = (int)(x1 - x0);  // items of the range
     const int nkb = P.nblocks, tiles = (int)P.dtiles.d;
     const int kb0 = nkb * part / KW, kcount = nkb * (part + 1) / KW - kb0;  // this wavefront's K blocks
-    const int mine_n = sub < n ? (n - sub + NC - 1) / NC : 0;               // its items: x0 + sub, x0 + sub + NC, ...
-    const uint32_t xs = x0 + (sub < n ? sub : 0);
+    const int mine_n = NC == 1 ? n : sub < n ? (n - sub + NC - 1) / NC : 0;  // its items: x0 + sub, x0 + sub + NC, ...
+    const uint32_t xs = NC == 1 ? x0 : x0 + (sub < n ? sub : 0);
     const int u0 = (int)P.dtiles(xs), it0 = (int)xs - u0 * tiles;
 
-    // The wavefront's next item: its tile and expert; whether the expert is another.
-    auto step = [&](int &t, int &u) {
-        t += NC;
-        if (t < tiles) return false;
-        do {
-            t -= tiles;
-            ++u;
-        } while (NC > 1 && t >= tiles);
-        return true;
+    // On to the wavefront's next item, tile t of expert u; `enter` is called if that is another expert (and there
+    // are more items).
+    auto next_item = [&](int &t, int &u, bool more, auto &&enter) __attribute__((always_inline)) {
+        if constexpr (NC == 1) {
+            if (++t == tiles) {
+                t = 0;
+                if (more) enter(++u);
+            }
+        } else {
+            t += NC;
+            if (t < tiles) return;
+            do {
+                t -= tiles;
+                ++u;
+            } while (t >= tiles);
+            if (more) enter(u);
+        }
     };
 
     // Load cursor: the item whose weights are being issued.  Offsets are scalar: a load's address is its
@@ -225,7 +242,7 @@ void expert_small_kernel(SmallParams P)
     uint32_t wj = (uint32_t)ct * tstride + (uint32_t)kb0 * kstride;
     auto advance = [&]() {
         ++ci;
-        if (step(ct, cu) && ci < mine_n) set_expert(cu);
+        next_item(ct, cu, ci < mine_n, set_expert);
         jhi = ci < mine_n ? kcount : 0;
         wj = (uint32_t)ct * tstride + (uint32_t)kb0 * kstride;
     };
@@ -380,7 +397,7 @@ void expert_small_kernel(SmallParams P)
                             u32x2{pack_bf16x2(h[0], h[1]), pack_bf16x2(h[2], h[3])};
                     }
                 }
-                if (step(bt, bu) && i + 1 < mine_n) load_b(bu);
+                next_item(bt, bu, i + 1 < mine_n, load_b);
             }
         }
     }
@@ -491,25 +508,33 @@ __global__ __launch_bounds__(256) void combine_small_kernel(VerifyArgs a)
 
 // ----------------------------------------------------------------------------- host side
 
-// Wavefronts that share an item: eight, or for short reductions the fewest that leave each at most two rounds.  With
-// eight throughout, reductions of up to eight blocks left wavefronts without a block and paid the item's barrier for
-// a few KiB, at least 0.7 us per item: 128 experts of 128 x 8192 (T = 16) took 235 us in bf16, 204 in FP8 and 191 in MXFP4
-// (the general kernels 141, 100 and 106), now 134, 72 and 54; 640 x 2176 in MXFP4 85 (general 83), now 65; 2048 x 768 in
-// MXFP4 74 (general 71), now 66.
-static int waves_per_item(int nblocks) { return nblocks <= 2 ? 1 : nblocks <= 4 ? 2 : nblocks <= 8 ? 4 : kSWaves; }
+// Wavefronts that share an item: eight, or, for reductions of up to eight blocks, the fewest that leave each at most
+// two rounds (bf16) or three (FP8, MXFP4, whose rounds are half and a quarter as long).  With eight throughout, such
+// reductions left wavefronts without a block and paid the item's barrier for a few KiB, at least 0.7 us per item: 128
+// experts of 128 x 8192 (T = 16) took 235 us in bf16, 204 in FP8 and 191 in MXFP4 (the general kernels 141, 100 and 106),
+// now 134, 72 and 54; 640 x 2176 in MXFP4 85 (general 83), now 65; 2048 x 768 in MXFP4 74 (general 71), now 66.  Three
+// rounds against two: 2048 x 768 in FP8 at T = 1 16.6 us against 17.5, in bf16 21.8 against 20.7.
+static int waves_per_item(int fmt, int nblocks)
+{
+    if (nblocks > 8) return kSWaves;
+    int kw = 1;
+    while ((nblocks + kw - 1) / kw > (fmt == FMT_BF16 ? 2 : 3)) kw *= 2;
+    return kw;
+}
 
 template <int FMT, bool DOWN>
 static hipError_t launch_projection(const SmallParams &p, int workers, hipStream_t stream)
 {
     const dim3 grid(workers), block(kSThreads);
-    const int kw = waves_per_item(p.nblocks), rounds = (p.nblocks + kw - 1) / kw;
+    const int kw = waves_per_item(FMT, p.nblocks), rounds = (p.nblocks + kw - 1) / kw;
     switch (kw * 16 + rounds) {
-#define SMALL_CASE(KW, J)                                                                          \
-    case KW * 16 + J:                                                                              \
-        hipLaunchKernelGGL((expert_small_kernel<FMT, DOWN, J, KW>), grid, block, 0, stream, p);    \
+#define SMALL_CASE(KW, J)                                                                              \
+    case KW * 16 + J:                                                                                  \
+        if constexpr (KW == kSWaves || J <= 2 || FMT != FMT_BF16)                                      \
+            hipLaunchKernelGGL((expert_small_kernel<FMT, DOWN, J, KW>), grid, block, 0, stream, p);    \
         break;
-        SMALL_CASE(1, 1) SMALL_CASE(1, 2) SMALL_CASE(2, 2) SMALL_CASE(4, 2) SMALL_CASE(8, 2) SMALL_CASE(8, 3)
-        SMALL_CASE(8, 4) SMALL_CASE(8, 5) SMALL_CASE(8, 6) SMALL_CASE(8, 7) SMALL_CASE(8, 8)
+        SMALL_CASE(1, 1) SMALL_CASE(1, 2) SMALL_CASE(1, 3) SMALL_CASE(2, 2) SMALL_CASE(2, 3) SMALL_CASE(4, 2)
+        SMALL_CASE(8, 2) SMALL_CASE(8, 3) SMALL_CASE(8, 4) SMALL_CASE(8, 5) SMALL_CASE(8, 6) SMALL_CASE(8, 7) SMALL_CASE(8, 8)
 #undef SMALL_CASE
     default: return hipErrorInvalidValue;
     }
