@@ -1,5 +1,5 @@
 """Weight packing at the edges of the kernel's runs along K (runs of 4 blocks, 32 blocks a turn of the workgroup) and of
-the last block, for the three layouts, against the numpy statement of the format in the parity tests; a guard behind
+the last block, and on both sides of its three splits (few tiles, small tiles, a workgroup a tile), for the three layouts, against the numpy statement of the format in the parity tests; a guard behind
 every output stays untouched."""
 import numpy as np
 import pytest
@@ -53,3 +53,12 @@ def test_layouts(fmt, N, K):
         assert np.array_equal(dp.cpu().numpy(), np.ascontiguousarray(tiles).reshape(-1))
         if sb:
             assert np.array_equal(dsp.cpu().numpy(), es)
+
+
+# More than 256 row tiles: a wavefront a tile up to 4 KiB of source (also with tiles left over from the last workgroup's
+# eight), beyond that a workgroup a tile, with one run, several, and more than a turn of them.
+@pytest.mark.parametrize("fmt,N,K", [(0, 2064, 32), (0, 2080, 64), (0, 2064, 128), (0, 2080, 160), (0, 2064, 4224), (1, 2176, 128),
+                                     (1, 2176, 256), (1, 2176, 384), (1, 2176, 4224), (2, 2080, 32), (2, 2064, 256), (2, 2080, 544),
+                                     (2, 2080, 4640)])
+def test_layouts_of_many_tiles(fmt, N, K):
+    test_layouts(fmt, N, K)
