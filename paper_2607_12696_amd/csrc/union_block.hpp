@@ -13,10 +13,15 @@
 // Up to 4096 slots (a verification batch of 512 tokens x 8) every pass stays in
 // registers: the slots are loaded and matched once, the counts of all passes
 // lie side by side in LDS, and one pass of scans gives first grouped and union
-// positions.  At 1600 slots, union and token-group plan in one launch: 5.9 us;
-// the union alone took 8.4 us with the separate counting and placement sweeps
-// that larger batches keep, which load and match every slot twice.
+// positions (one scan of both: slots and used experts below 2^16).  At 1600
+// slots, union and token-group plan in one launch: 5.9 us; the union alone took
+// 8.4 us with the separate counting and placement sweeps that larger batches
+// keep, which load and match every slot twice.  A single pass (1024 slots) keeps
+// its counts in 32 bits: 16-bit LDS accesses and a scan each for slots and
+// experts took 0.3 us more (E = 256, 512 slots: 3.6 us, now 3.3).
 #pragma once
+
+#include <type_traits>
 
 #include "device.hpp"
 
@@ -29,7 +34,7 @@ constexpr int kUnionPasses = 4;  // passes held in registers
 struct UnionLds {
     union {
         uint16_t wcnt16[kUnionPasses][kUnionWaves][kUnionThreads];  // per-pass, per-wavefront counts, then positions
-        int wcnt[kUnionWaves][kUnionThreads];                       // beyond kUnionPasses: of the current pass
+        int wcnt[kUnionWaves][kUnionThreads];                       // of the only, or (beyond kUnionPasses) the current pass
     };
     int member_id[kUnionThreads];
     int member_start[kUnionThreads];
@@ -56,14 +61,14 @@ __device__ __forceinline__ void union_members(UnionLds &L, int E, int c, int pos
     }
 }
 
-__device__ __forceinline__ void union_write(const UnionLds &L, int E, int32_t *__restrict__ union_ids,
+__device__ __forceinline__ void union_write(const UnionLds &L, int E, int U, int placed, int32_t *__restrict__ union_ids,
                                             int32_t *__restrict__ n_unique, int32_t *__restrict__ offsets)
 {
     for (int u = threadIdx.x; u <= E; u += kUnionThreads) {
-        if (u < E) union_ids[u] = u < L.U ? L.member_id[u] : -1;
-        offsets[u] = u < L.U ? L.member_start[u] : L.placed;
+        if (u < E) union_ids[u] = u < U ? L.member_id[u] : -1;
+        offsets[u] = u < U ? L.member_start[u] : placed;
     }
-    if (threadIdx.x == 0) *n_unique = L.U;
+    if (threadIdx.x == 0) *n_unique = U;
 }
 
 // S <= PASSES * 1024 slots.
@@ -73,6 +78,11 @@ __device__ __forceinline__ void union_in_registers(UnionLds &L, const int32_t *_
                                                    int32_t *__restrict__ n_unique, int32_t *__restrict__ offsets,
                                                    int32_t *__restrict__ perm)
 {
+    using count_t = std::conditional_t<PASSES == 1, int, uint16_t>;
+    auto at = [&](int p, int w, int e) -> count_t & {
+        if constexpr (PASSES == 1) return L.wcnt[w][e];
+        else return L.wcnt16[p][w][e];
+    };
     const int tid = threadIdx.x, wave = tid / kWave;
     int e[PASSES], rank[PASSES];
 #pragma unroll
@@ -80,39 +90,41 @@ __device__ __forceinline__ void union_in_registers(UnionLds &L, const int32_t *_
     if (tid < E)
 #pragma unroll
         for (int p = 0; p < PASSES; ++p)
-            for (int w = 0; w < kUnionWaves; ++w) L.wcnt16[p][w][tid] = 0;
+            for (int w = 0; w < kUnionWaves; ++w) at(p, w, tid) = 0;
     __syncthreads();
 #pragma unroll
     for (int p = 0; p < PASSES; ++p) {
         bool top;
         int cnt;
         wave_match(e[p], (unsigned)e[p] < (unsigned)E, nbits, rank[p], top, cnt);
-        if (top) L.wcnt16[p][wave][e[p]] = (uint16_t)cnt;
+        if (top) at(p, wave, e[p]) = (count_t)cnt;
     }
     __syncthreads();
     int c = 0;
     if (tid < E)
 #pragma unroll
         for (int p = 0; p < PASSES; ++p)
-            for (int w = 0; w < kUnionWaves; ++w) c += L.wcnt16[p][w][tid];
-    int pos, start, U, placed;
-    block_exclusive_scan2(c > 0 ? 1 : 0, c, L.wave_tot, pos, start, U, placed);
+            for (int w = 0; w < kUnionWaves; ++w) c += at(p, w, tid);
+    static_assert(kUnionPasses * kUnionThreads < 1 << 15, "slots and experts in one word");
+    int tot = 0;
+    const int ex = block_exclusive_scan((c << 16) | (c > 0 ? 1 : 0), L.wave_tot, &tot);
+    const int pos = ex & 0xffff, start = ex >> 16, U = tot & 0xffff, placed = tot >> 16;
     union_members(L, E, c, pos, start, U, placed, counts);
     if (tid < E) {  // counts -> first position of each pass's and wavefront's slots (below 4096)
         int run = start;
 #pragma unroll
         for (int p = 0; p < PASSES; ++p)
             for (int w = 0; w < kUnionWaves; ++w) {
-                const int n = L.wcnt16[p][w][tid];
-                L.wcnt16[p][w][tid] = (uint16_t)run;
+                const int n = at(p, w, tid);
+                at(p, w, tid) = (count_t)run;
                 run += n;
             }
     }
     __syncthreads();
-    union_write(L, E, union_ids, n_unique, offsets);
+    union_write(L, E, U, placed, union_ids, n_unique, offsets);
 #pragma unroll
     for (int p = 0; p < PASSES; ++p)
-        if ((unsigned)e[p] < (unsigned)E) perm[L.wcnt16[p][wave][e[p]] + rank[p]] = p * kUnionThreads + tid;
+        if ((unsigned)e[p] < (unsigned)E) perm[at(p, wave, e[p]) + rank[p]] = p * kUnionThreads + tid;
 }
 
 // The union, scans and grouping of S routed slots idx[0 .. S), by the whole 1024-thread workgroup; U, placed and
@@ -157,7 +169,7 @@ __device__ __forceinline__ void union_block(UnionLds &L, const int32_t *__restri
     block_exclusive_scan2(c > 0 ? 1 : 0, c, L.wave_tot, pos, start, U, placed);
     union_members(L, E, c, pos, start, U, placed, counts);
     __syncthreads();
-    union_write(L, E, union_ids, n_unique, offsets);
+    union_write(L, E, U, placed, union_ids, n_unique, offsets);
 
     // 3. Placement, pass by pass: thread e turns the per-wavefront counts into
     //    first positions (in place), then every slot of the pass is placed.
