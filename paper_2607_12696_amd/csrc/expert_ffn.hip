@@ -1420,22 +1420,35 @@ __device__ __forceinline__ void plan_block(UnionLds &L, const VerifyArgs &a, int
 
 constexpr int kQuantThreads = 256;
 
-// What the expert launches of a call need first, in one launch: workgroup 0 builds the union and the token-group
-// plan (T > 64; `grouped`), the others quantise x (MX activations; kpd = 0: none).  As three launches these took
-// 7.5 + 4.6 + 5.7 us (1200 slots, 300 rows of 2880), together 6.8.
-__global__ __launch_bounds__(kUnionThreads) void prepare_kernel(VerifyArgs a, int grouped, int32_t *plan, int kpd)
+// x quantised (MX activations), where the call has no union to build first (T <= 64) or many rows.
+__global__ __launch_bounds__(kQuantThreads) void mx_quant_kernel(VerifyArgs a, int kpd)
+{
+    mx_quant_block(a.x, a.T, a.d, kpd, a.xq, a.xs, (int)(blockIdx.x * kQuantThreads + threadIdx.x));
+}
+
+// What the expert launches of a call of more than 64 tokens need first: workgroup 0 builds the union and the
+// token-group plan, the others, if any, quantise x (MX activations).  As three launches these took 7.5 + 4.6 + 5.7 us
+// (1200 slots, 300 rows of 2880), together 6.8.  A quantising workgroup of this launch holds the union's LDS, so a
+// compute unit runs one at a time; quant_merged() says up to how many that is no loss.
+__global__ __launch_bounds__(kUnionThreads) void prepare_kernel(VerifyArgs a, int32_t *plan, int kpd)
 {
     __shared__ UnionLds L;
     fetch_args(a);
-    if (grouped && blockIdx.x == 0) {
+    if (blockIdx.x == 0) {
         union_block(L, a.topk_idx, a.T * a.k, a.E, a.counts, a.union_ids, a.n_unique, a.offsets, a.perm);
         plan_block(L, a, plan);
         return;
     }
     // A quarter of the threads quantise: more, lighter workgroups (8.8 -> 6.8 us for 300 rows of 2880).
     if (threadIdx.x < kQuantThreads)
-        mx_quant_block(a.x, a.T, a.d, kpd, a.xq, a.xs, (int)((blockIdx.x - grouped) * kQuantThreads + threadIdx.x));
+        mx_quant_block(a.x, a.T, a.d, kpd, a.xq, a.xs, (int)((blockIdx.x - 1) * kQuantThreads + threadIdx.x));
 }
+
+// Quantising workgroups up to which they go into the union's launch: what the compute units run beside it, about 1.25
+// rounds of them (of 2.7 us each) per 1024 slots.  Whole passes, d_ff = 512, one expert a token, merged and in a launch
+// of their own: d = 8192, T = 65 46 and 50 us, 300 70 and 70, 512 81.7 and 80.5, 1024 111 and 104, 4096 350 and 308; 4 of 128
+// GPT-OSS experts a token, T = 4096 (1472 workgroups, 16384 slots) 935 and 947.
+static bool quant_merged(int workgroups, int slots) { return workgroups <= 320 * ((slots + 1023) / 1024); }
 
 // A row of a down item cut over two or three ranges (descriptor kind 1): its
 // parked partial sums, all loads issued at once (absent ones read zeros) and
@@ -1669,11 +1682,15 @@ static hipError_t launch_fmt(const VerifyArgs &args, uint8_t *ws_base, const Ver
         a.hq = a.xs + align((size_t)a.T * kpd / 32);
         a.hs = a.hq + align(rows * kpf);
     }
-    if (grouped || MXA) {
-        // The token-group plan needs the union first; without it the gate/up kernel builds the union itself.
-        const int quant = (a.T * (kpd / 32) + kQuantThreads - 1) / kQuantThreads;
-        hipLaunchKernelGGL(prepare_kernel, dim3((grouped ? 1 : 0) + quant), dim3(kUnionThreads), 0, stream, a, grouped ? 1 : 0,
-                           plan, kpd);
+    // The token-group plan needs the union first; without it the gate/up kernel builds the union itself.
+    const int quant = (a.T * (kpd / 32) + kQuantThreads - 1) / kQuantThreads;  // workgroups (0 without MX activations)
+    const bool merged = grouped && quant_merged(quant, a.T * a.k);
+    if (grouped) {
+        hipLaunchKernelGGL(prepare_kernel, dim3(1 + (merged ? quant : 0)), dim3(kUnionThreads), 0, stream, a, plan, kpd);
+        if ((err = hipGetLastError()) != hipSuccess) return err;
+    }
+    if (quant > 0 && !merged) {
+        hipLaunchKernelGGL(mx_quant_kernel, dim3(quant), dim3(kQuantThreads), 0, stream, a, kpd);
         if ((err = hipGetLastError()) != hipSuccess) return err;
     }
     if ((err = mark(events, 0, stream)) != hipSuccess) return err;
