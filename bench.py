@@ -204,7 +204,7 @@ class Runner:
 
     def __init__(self, layer, T, act_fmt=0):
         torch, moe, sh = layer.torch, layer.moe, layer.sh
-        self.layer, self.T, self.torch, self.moe, self.sh = layer, T, torch, moe, sh
+        self.layer, self.T, self.torch, self.moe, self.sh, self.act_fmt = layer, T, torch, moe, sh, act_fmt
         dev = layer.dev
         self.wds = [dict(w, act_fmt=act_fmt) for w in layer.wdicts]
         self.x = layer.synth.activations(T, sh.d, seed=1, device=dev)
@@ -285,6 +285,8 @@ class Runner:
         torch.cuda.synchronize()
         spans = {"step": (0, 5), "route": (0, 1), "verify": (1, 5), "gateup": (1, 2), "gateup_fixup": (2, 3),
                  "down": (3, 4), "combine": (4, 5)}
+        if self.T <= 16 and not self.act_fmt:
+            del spans["gateup_fixup"]  # small calls launch no fix-up: that interval is empty
         return {k: [e[a].elapsed_time(e[b]) for e in evs] for k, (a, b) in spans.items()}
 
 
@@ -362,7 +364,7 @@ def token_sweep(layer, Ms=(1, 4, 16, 32, 64), U=32, steps=20, warmup=None, n_poo
         per = rn.time_marks(pool, steps, 0)
         med = {k: 1e3 * pct(v, 0.5) for k, v in per.items()}
         gu, dn = kernel_alg_bytes(sh, T, U, False), kernel_alg_bytes(sh, T, U, True)
-        pt = {"M": M, "T": T, "step_us": step_us, "gateup_us": med["gateup"], "fixup_us": med["gateup_fixup"],
+        pt = {"M": M, "T": T, "step_us": step_us, "gateup_us": med["gateup"], "fixup_us": med.get("gateup_fixup"),
               "down_us": med["down"], "combine_us": med["combine"],
               "gateup_GB_s": gu / (med["gateup"] * 1e-6) / 1e9, "down_GB_s": dn / (med["down"] * 1e-6) / 1e9,
               "step_GB_s": n_exp * expert_bytes(sh) / (step_us * 1e-6) / 1e9}

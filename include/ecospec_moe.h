@@ -349,6 +349,12 @@ moe_status_t moe_verify_layer_noalloc(const void *x, const moe_weights_t *w, con
  *   events[0] before the gate/up expert kernel, events[1] after it (before
  *   its fix-up kernel), events[2] before the down expert kernel, events[3]
  *   after it (before the combine kernel), events[4] after the combine kernel.
+ * With MX activations events[0] precedes the kernel that quantises x (which
+ * for some calls of more than 64 tokens builds the union and the token-group
+ * plan as well); without, the union of a call of more than 64 tokens is built
+ * before events[0].  Calls of up to 16 tokens without MX activations, d and
+ * d_ff up to 8192, have no fix-up kernel: nothing runs between events[1] and
+ * events[2].
  * events is an array of 5 hipEvent_t handles created by the caller (any
  * entry may be NULL to skip that mark).
  */

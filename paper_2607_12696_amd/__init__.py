@@ -437,8 +437,8 @@ def moe_verify_layer_noalloc(x, weights: dict, routing: Routing, y=None):
 
 def moe_verify_layer_timed(x, weights: dict, routing: Routing, y, workspace, events):
     """moe_verify_layer that also records 5 torch.cuda.Event marks on the current stream:
-    before the gate/up expert kernel, after it, before the down expert kernel, after it,
-    after the combine kernel."""
+    before the gate/up expert kernel (MX activations: before the quantisation of x), after it,
+    before the down expert kernel, after it, after the combine kernel."""
     if len(events) != 5:
         raise ValueError("moe_verify_layer_timed takes 5 events")
     arr = (C.c_void_p * 5)(*[e.cuda_event if e is not None else None for e in events])

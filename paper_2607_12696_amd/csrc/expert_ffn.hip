@@ -1685,15 +1685,18 @@ static hipError_t launch_fmt(const VerifyArgs &args, uint8_t *ws_base, const Ver
     // The token-group plan needs the union first; without it the gate/up kernel builds the union itself.
     const int quant = (a.T * (kpd / 32) + kQuantThreads - 1) / kQuantThreads;  // workgroups (0 without MX activations)
     const bool merged = grouped && quant_merged(quant, a.T * a.k);
+    // The first mark precedes the quantisation of x, which is part of what the projections cost.
+    const bool mark_first = quant > 0 && (merged || !grouped);
+    if (mark_first && (err = mark(events, 0, stream)) != hipSuccess) return err;
     if (grouped) {
         hipLaunchKernelGGL(prepare_kernel, dim3(1 + (merged ? quant : 0)), dim3(kUnionThreads), 0, stream, a, plan, kpd);
         if ((err = hipGetLastError()) != hipSuccess) return err;
     }
+    if (!mark_first && (err = mark(events, 0, stream)) != hipSuccess) return err;
     if (quant > 0 && !merged) {
         hipLaunchKernelGGL(mx_quant_kernel, dim3(quant), dim3(kQuantThreads), 0, stream, a, kpd);
         if ((err = hipGetLastError()) != hipSuccess) return err;
     }
-    if ((err = mark(events, 0, stream)) != hipSuccess) return err;
     FfnParams g{};
     g.a = a;
     g.N = a.d_ff;

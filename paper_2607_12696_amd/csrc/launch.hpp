@@ -83,7 +83,7 @@ int verify_workers();
 // the grid the call will launch (the partial-sum slots are sized by it).
 VerifyWorkspace verify_workspace(int d, int d_ff, int T, int k, bool shared, bool mx, int workers);
 
-// events: kTimingMarks optional marks (before gate/up, before its fix-up, before
+// events: kTimingMarks optional marks (before gate/up and the quantisation of x, before its fix-up, before
 // down, before combine, after combine).
 hipError_t launch_verify(const VerifyArgs &a, void *workspace, const VerifyWorkspace &ws, hipStream_t stream,
                          hipEvent_t const *events = nullptr);
