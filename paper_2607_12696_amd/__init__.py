@@ -134,9 +134,18 @@ def _torch():
 # (0.1 us; torch.cuda.current_stream builds a Stream object, 1.9 us), the C structs are built by one constructor call,
 # and a routing's integer arrays come from one allocation.
 
+_raw_stream = None  # device index -> handle of its current stream
+
+
 def _stream(t) -> int:
     """Handle of the current stream of t's device (t is a device tensor)."""
-    return _torch()._C._cuda_getCurrentRawStream(t.get_device())
+    global _raw_stream
+    if _raw_stream is None:
+        torch = _torch()
+        # Not part of torch's public interface: a torch without it takes the public way.
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+            lambda device: torch.cuda.current_stream(device).cuda_stream)
+    return _raw_stream(t.get_device())
 
 
 def _dev_ptr(t, what: str) -> int:
