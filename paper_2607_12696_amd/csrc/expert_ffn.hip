@@ -1,4 +1,6 @@
-// Grouped SwiGLU experts of the verification pass on gfx950 (CDNA4).
+// Grouped SwiGLU experts of the verification pass on gfx950 (CDNA4): the general
+// kernels, for calls of more than 16 tokens, with MX activations, or of more than
+// 64 K blocks (d or d_ff above 8192); expert_small.hip has the other calls'.
 //
 // The pass is bound by HBM bandwidth: every distinct expert routed to by the
 // verified tokens must be read once, while each weight serves only the M_u
@@ -1265,8 +1267,10 @@ void expert_ffn_kernel(FfnParams P)
 // kernel boundary makes the expert kernel's records and partial sums visible
 // here.  Two round trips (record, partial sums) and little code, since every
 // instruction is fetched cold: with all four token blocks unrolled in one
-// workgroup and the record read field by field it took
-// 6.2 us (GPT-OSS, 64 tokens), 7.3 (with MX activations, 300) and 5.7 (DeepSeek, 64); now 5.5, 5.1 and 5.5.
+// workgroup and the record read field by field it took 6.2 us (GPT-OSS, 64
+// tokens, tree routing), 7.3 (with MX activations, 300 scattered) and 5.7
+// (DeepSeek, 64 on 32 experts); now 5.5, 5.1 and 5.5.  GPT-OSS, 64 tokens on 32
+// experts, takes 4.7 either way.
 template <bool MXA>
 __global__ __launch_bounds__(kThreads) void expert_ffn_fixup_kernel(FfnParams P)
 {

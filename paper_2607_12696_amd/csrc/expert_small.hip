@@ -16,10 +16,12 @@
 // activations those blocks need (16 tokens x 128 elements each) therefore stay
 // in registers, as matrix-core operands, for all items of an expert: no
 // activation tiles, and no barrier per step.  The partial sums of an item are
-// added through LDS, in wavefront order, by one wavefront (a
-// different one each item), behind the item's one barrier.  Dealing the blocks
-// round-robin instead (a round then reads 32 contiguous KiB) measured the same
-// to 2% slower; rings of half or twice the depth are no faster.
+// added through LDS, in wavefront order, by one wavefront (a different one each
+// item), behind the item's one barrier.  So a sum over K is up to eight partial
+// sums in fp32, where the general kernels add it up in one: single values of y
+// differ by a bf16 step, at the same distance from a 64-bit result.  Dealing the
+// blocks round-robin instead (a round then reads 32 contiguous KiB) measured the
+// same to 2% slower.
 //
 // Split.  The items of a launch (expert-major) are cut into contiguous ranges
 // of whole items, one per workgroup, in closed form from the number of distinct
@@ -27,25 +29,30 @@
 // workgroups and so no fix-up launch.  A range is at most one item longer than
 // another; the workgroups still streaming then share the bandwidth of the idle
 // ones.  Cutting gate/up items at K blocks where that idle time looked long,
-// with the pieces added by the down launch, was slower wherever it applied:
-// Qwen T = 4 on 13 experts 83.6 -> 88.6 us, one Qwen expert (96 items on 256
-// workgroups) 22.8 -> 32.9 us.  Cutting down items between their two row tiles
-// gained nothing either (GPT-OSS T = 16 on 16 experts 50.8 -> 51.8 us).
+// with the pieces added by the down launch, was slower wherever it applied (the
+// launches of one call, without the router, replayed from a graph): Qwen T = 4 on
+// 13 experts 83.6 -> 88.6 us, one Qwen expert (96 items on 256 workgroups) 22.8 ->
+// 32.9 us.  Cutting down items between their two row tiles gained nothing either
+// (GPT-OSS T = 16 on 16 experts 50.8 -> 51.8 us).
 //
 // H and O rows sit at the routed slots (t * k + j; the shared expert's at
 // T * k + t).  A launch needs no grouping: the distinct experts are a bit set
 // in LDS and an expert's slots are found with ballots.  An expert of more than
 // 16 slots takes part once more for each further 16 (`extra`, built only if one
-// of the slots' counts says so).  The routing arrays of
-// the caller (counts, union, offsets, perm) are written by one extra workgroup
-// of the combine launch, beside the others.
+// of the slots' counts says so).  The routing arrays of the caller (counts,
+// union, offsets, perm) are written by one extra workgroup of the combine launch,
+// beside the others.
 //
-// Measured against the general kernels (whole pass, same box): GPT-OSS layer
-// T = 1 47.3 -> 27.9 us (with a leaner host call), T = 4 (8-layer graph, with its
-// router) 592 -> 427 us; Qwen layer T = 4 108.9 -> 89.2 us; DeepSeek layer T = 4 on
-// 31 experts 236.2 -> 228.1 us, T = 16 330 -> 307 us.  At T = 16 each further
-// expert streams at 6.4 (FP8), 6.5 (bf16) and 6.7 TB/s (MXFP4; 6.3 before); what
-// is left above the stream is about 20 us a pass (35 to 40 before).
+// Measured against the general kernels, timed in turn on one box.  Whole calls
+// through the Python binding: GPT-OSS T = 1 47.2 -> 27.0 us (with a leaner host
+// call), 8 GPT-OSS layers with their routers at T = 4 in one graph 596 -> 437 us,
+// Qwen T = 4 (tree routing) 104 -> 84 us, DeepSeek T = 4 on 31 experts 243 -> 232 us,
+// T = 16 (tree routing) 357 -> 331 us.  The launches of one call, without router and
+// shared expert, replayed from a graph: DeepSeek T = 4 on 31 experts 236.6 -> 214.5
+// us, T = 16 on 43 318.6 -> 302.2 us; Qwen T = 16 on 64 379.8 -> 380.1 us; GPT-OSS
+// T = 16 on 48 130.9 -> 109.3 us.  At T = 16 each further expert streams at 6.4 (FP8),
+// 6.5 (bf16) and 6.7 TB/s (MXFP4; 6.3 before); what is left above the stream is
+// about 20 us a call (35 to 40 before).
 #include "expert_common.hpp"
 
 namespace ecospec {
