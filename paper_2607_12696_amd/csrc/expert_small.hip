@@ -519,7 +519,7 @@ __global__ __launch_bounds__(256) void combine_small_kernel(VerifyArgs a)
 // two rounds (bf16) or three (FP8, MXFP4, whose rounds are half and a quarter as long).  With eight throughout, such
 // reductions left wavefronts without a block and paid the item's barrier for a few KiB, at least 0.7 us per item: 128
 // experts of 128 x 8192 (T = 16) took 235 us in bf16, 204 in FP8 and 191 in MXFP4 (the general kernels 141, 100 and 106),
-// now 134, 72 and 54; 640 x 2176 in MXFP4 85 (general 83), now 65; 2048 x 768 in MXFP4 74 (general 71), now 66.  Three
+// now 132, 70 and 52; 640 x 2176 in MXFP4 84 (general 83), now 57; 2048 x 768 in MXFP4 74 (general 71), now 63.  Three
 // rounds against two: 2048 x 768 in FP8 at T = 1 16.6 us against 17.5, in bf16 21.8 against 20.7.
 static int waves_per_item(int fmt, int nblocks)
 {

@@ -349,8 +349,8 @@ SMALL = {
     "fp8_wide": synth.Shape("fp8_wide", 384, 128, 8, 2, synth.FMT_FP8, 1, True),
     "mxfp4": synth.Shape("mxfp4", 320, 160, 16, 4, synth.FMT_MXFP4, 0, False),
     "one": synth.Shape("one", 64, 32, 1, 1, synth.FMT_BF16, 0, False),
-    # Few units per launch, so one item is spread over many workgroups (16 at T = 1 on 256 of them): the
-    # finishing of cut items walks the ranges instead of reading three packed slots.
+    # Few units per launch, so in the general kernels (T > 16) one item is spread over many workgroups (16 with
+    # one expert on 256 of them): the finishing of cut items walks the ranges instead of reading three packed slots.
     "wide": synth.Shape("wide", 2048, 2048, 4, 1, synth.FMT_BF16, 0, False),
     "wide_fp8": synth.Shape("wide_fp8", 1024, 1024, 4, 1, synth.FMT_FP8, 1, True),
 }
@@ -383,8 +383,9 @@ def test_verify_small_matches_oracle(name, T):
 
 def test_wide_shapes_spread_items_over_more_than_three_workgroups():
     # The split of this device's grid (one workgroup per compute unit) puts more than three ranges on the
-    # items of the wide shapes at T = 1, so their parity runs above finish cut items by walking the ranges
-    # (gate/up fix-up and combine alike).
+    # items of the wide shapes with one token per expert, and so with up to 16.  Calls of up to 16 tokens cut no
+    # item; the parity runs that finish such items by walking the ranges (gate/up fix-up and combine alike) are
+    # those of more tokens, test_gpu_wide_items.py's among them.
     from test_split_bookkeeping import brute_owner, kernel_costs
     W = min(torch.cuda.get_device_properties(0).multi_processor_count, 512)
     for fmt, n_exp, nbands, nsteps in [("bf16", 1, 16, 16), ("bf16", 1, 8, 16),   # wide: gate/up, down
@@ -636,8 +637,8 @@ _union_layers = {}
 @pytest.mark.parametrize("T", [1, 8, 64, 130])
 @pytest.mark.parametrize("bad", [False, True])
 def test_verify_builds_the_union_itself(name, T, bad):
-    # The verification writes the union and grouping of Eq. 1 itself (in the gate/up kernel for T <= 64, by
-    # the union kernel beyond): from a bare top-k, with garbage in the union arrays, it gives the oracle's
+    # The verification writes the union and grouping of Eq. 1 itself (beside the combine for T <= 16, in the
+    # gate/up kernel for T <= 64, in the launch before it beyond): from a bare top-k, with garbage in the union arrays, it gives the oracle's
     # union and grouping bit for bit and the same y as from moe_expert_union's routing.  bad: some slots
     # name an expert outside [0, E); they are never placed and add nothing.
     sh = UNION_SHAPES[name]
