@@ -20,11 +20,9 @@ from test_split_bookkeeping import brute_owner, kernel_costs
 DEV = torch.device("cuda:0")
 
 
-@pytest.mark.parametrize("fmt,size,shared", [(0, 2048, False), (1, 1024, True), (2, 2048, False), (2, 1024, True)])
-@pytest.mark.parametrize("mx", [False, True])
+@pytest.mark.parametrize("fmt,size,shared,mx", [(0, 2048, False, False), (1, 1024, True, False), (2, 2048, False, False),
+                                                (2, 1024, True, False), (2, 2048, False, True), (2, 1024, True, True)])
 def test_items_over_more_than_three_workgroups(fmt, size, shared, mx):
-    if mx and fmt != synth.FMT_MXFP4:
-        pytest.skip("MX activations take MXFP4 weights")
     T, E = 17, 3
     note(f"wide items fmt={fmt} size={size} shared={shared} mx={mx}")
     W = min(torch.cuda.get_device_properties(0).multi_processor_count, 512)
